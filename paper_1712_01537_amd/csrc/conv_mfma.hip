@@ -32,6 +32,7 @@
 #include "pool_fuse.h"
 
 #include "conv_cin.h"
+#include "conv_split.h"
 
 #include <algorithm>
 #include <cmath>
@@ -398,303 +399,6 @@ __global__ __launch_bounds__(TB) void k_conv_tile(const int32_t* __restrict__ nb
         acc[mr][nr] = v4f{0.f, 0.f, 0.f, 0.f};
       }
     }
-  }
-}
-
-// ---------------------------------------------------------------------------
-// Stride-1, K = 3 convolution, weights in registers (k_conv_tile3):
-// out[i][n] = sum_k sum_c x[nb(i,k)][c] W'[k][c][n] for the 16-channel chunk
-// c0 = 16 blockIdx.z of the reduction (partial sums when there are several).
-// The MFMA computes out^T: A = W'^T (16 output channels x 4 reduction
-// channels), B = the gathered rows (4 channels x 16 octants).  Each wave
-// keeps the chunk's weights of its 16 output channels in registers for the
-// whole launch (27 taps x 4 channels per lane), so the only LDS traffic is
-// the group tiles: one 16-byte read per lane feeds four MFMAs.
-// Workgroups (two or three per CU) are persistent over a contiguous range of
-// sibling groups, taken in tiles of GPB groups (GPB/2 blocks of 16 rows).
-// Wave w takes output channels 16 (w % WN).. and row blocks RB (w / WN) + r,
-// r < RB; in the range's last tile, which may be partial, the live row
-// blocks are dealt round the WM waves of a column instead.  The
-// (K+1)^3 x 16-channel group tiles are streamed with direct global->LDS
-// loads into two static buffers: tile t+1 lands while tile t is multiplied,
-// with one barrier per tile.  Absent neighbours and channels past kk read a
-// zero row.
-// Group tile layout, in 16-byte chunks: group g at 280 g, x-slab at 68 x,
-// position (y, z) at slot 4y + z, channel quad f stored at f ^ ((y + 2z) & 3).
-// A read of one tap by 8 (or 16) lanes touches 2 slabs x 2 y x 2 z positions
-// (of 1 or 2 groups) at one quad; the quad swizzle and the strides (68 = 4
-// mod 8, 280 = 8 mod 16) put them on distinct banks whether the LDS serves 8
-// lanes from 32 banks or 16 lanes from 64.  Each x-slab of a group (16
-// positions x 4 quads) is one wave's load instruction.
-// FLIP: input gradient, W'[k][c][n] = W[26-k][n][c].
-// POOL (forward only, one reduction chunk): the 2x2x2 max-pool follows the
-// (ReLU'd) output in the epilogue, through a small LDS area per wave; out
-// is then the pooled map [npar][nn] of depth l-1 (row prow[g] for group g,
-// loaded a tile ahead), psw the switches [ngroups][nn], and the workgroups
-// of column block 0 zero an equal share of the rows of empty depth-(l-1)
-// octants (plab[i] == 0).
-template <int WN, int GPB, bool FLIP, bool POOL>
-__global__ __launch_bounds__(TB) __attribute__((amdgpu_waves_per_eu(2))) void k_conv_tile3(const int32_t* __restrict__ nbr,
-                                                   int64_t ngroups, const float* __restrict__ x,
-                                                   int kk, const float* __restrict__ w, int nn,
-                                                   float* __restrict__ out, int relu,
-                                                   float* __restrict__ part,
-                                                   const int32_t* __restrict__ prow,
-                                                   const int32_t* __restrict__ plab, int64_t npar,
-                                                   uint8_t* __restrict__ psw) {
-  constexpr int K3 = 27, BN = 16 * WN, WM = WAVES / WN;
-  constexpr int RB = GPB / 2 / WM;  // row blocks per wave
-  static_assert(RB >= 1 && RB * WM * 2 == GPB, "every row block has one wave");
-  constexpr int GSTR = 280, XSTR = 68, BUFC = GPB * GSTR;  // in 16-byte chunks
-  __shared__ __attribute__((aligned(16))) v4f X0[BUFC];
-  __shared__ __attribute__((aligned(16))) v4f X1[BUFC];
-  __shared__ __attribute__((aligned(16))) float PS[WAVES][POOL ? oc::kPoolLdsFloats : 4];
-
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int li = lane & 15, q = lane >> 4;
-  const int wn = wave % WN, wm = wave / WN;
-  const int n0 = blockIdx.y * BN + 16 * wn, c0 = 16 * blockIdx.z;
-  const int nx = gridDim.x, bx = blockIdx.x;
-  const int lb = nx >= 8 ? (bx % 8) * (nx / 8) + bx / 8 : bx;  // XCD-contiguous ranges
-  const int64_t g0 = ngroups * lb / nx, g1 = ngroups * (lb + 1) / nx;  // groups [g0, g1)
-  const int T = (int)((g1 - g0 + GPB - 1) / GPB);
-  if constexpr (POOL) {
-    if (blockIdx.y == 0) {  // rows of empty depth-(l-1) octants
-      const int64_t r0 = npar * lb / nx, r1 = npar * (lb + 1) / nx;
-      const int c4 = nn / 4, cnt = (int)(r1 - r0) * c4;
-      for (int e = tid; e < cnt; e += TB) {
-        const int64_t i = r0 + e / c4;
-        if (plab[i] == 0)
-          *reinterpret_cast<v4f*>(out + i * nn + 4 * (e % c4)) = v4f{0.f, 0.f, 0.f, 0.f};
-      }
-    }
-  }
-  if (T <= 0) return;  // uniform over the workgroup
-  // pooled forward: the depth-(l-1) output row of this lane's group in each
-  // of its row blocks, loaded a tile ahead of the epilogue that stores it
-  int32_t prq[RB];
-  auto load_pr = [&](int t) {
-    if constexpr (POOL) {
-#pragma unroll
-      for (int r = 0; r < RB; ++r) {
-        const int64_t g = g0 + (int64_t)t * GPB + 2 * (wm * RB + r) + ((lane >> 4) & 1);
-        prq[r] = g < g1 ? prow[g] : -1;
-      }
-    }
-  };
-
-  // loads: wave w fills x-slab w of every group; lane -> chunk (slot 4y + z,
-  // stored quad), holding channel quad (stored ^ ((y + 2z) & 3))
-  const int py = lane >> 4, pz = (lane >> 2) & 3, px = wave;
-  const int f_ = (lane & 3) ^ ((py + 2 * pz) & 3);
-  const int ux = px - 1, uy = py - 1, uz = pz - 1;
-  const int l_slot = ((ux >> 1) + 1) * 9 + ((uy >> 1) + 1) * 3 + ((uz >> 1) + 1);
-  const int l_coff = 4 * (ux & 1) + 2 * (uy & 1) + (uz & 1);
-  const int l_ch = c0 + 4 * f_;
-  int32_t nbc[GPB], nbn[GPB];
-  uint32_t okc = 0, okn = 0;
-  auto load_nb = [&](int t, int32_t (&v)[GPB], uint32_t& ok) {
-    ok = 0;
-#pragma unroll
-    for (int i = 0; i < GPB; ++i) {
-      const int64_t g = g0 + (int64_t)t * GPB + i;
-      const bool live = t < T && g < g1;
-      v[i] = nbr[live ? 27 * g + l_slot : 0];
-      ok |= (uint32_t)live << i;
-    }
-  };
-  // lanes of absent rows write their zeros themselves (a shared zero row
-  // would put every absent lane of the grid on one cache line)
-  auto dma = [&](v4f* buf) {
-#pragma unroll
-    for (int i = 0; i < GPB; ++i) {
-      const bool live = ((okc >> i) & 1) && nbc[i] >= 0 && l_ch < kk;
-      v4f* blk = buf + i * GSTR + px * XSTR;
-      const uint32_t a = lds_addr(blk);
-      if (live)
-        lds_load16(x + (int64_t)(nbc[i] + l_coff) * kk + l_ch, a);
-      else
-        blk[lane] = v4f{0.f, 0.f, 0.f, 0.f};
-    }
-  };
-
-  // reads: lane (li, q) supplies row li of row block rb: child li & 7 of
-  // group 2 rb + (li >> 3), channels 4q..4q+3
-  int aoff[9];
-  {
-    const int g = 2 * (wm * RB) + (li >> 3), c = li & 7;
-    const int cx = c >> 2, cy = (c >> 1) & 1, cz = c & 1;
-#pragma unroll
-    for (int j = 0; j < 9; ++j) {
-      const int y = cy + j / 3, z = cz + j % 3;
-      aoff[j] = g * GSTR + cx * XSTR + 4 * (4 * y + z) + (q ^ ((y + 2 * z) & 3));
-    }
-  }
-
-  v4f acc0[RB], acc1[RB];
-#pragma unroll
-  for (int r = 0; r < RB; ++r) acc0[r] = acc1[r] = v4f{0.f, 0.f, 0.f, 0.f};
-  v4f wr[K3];  // this lane's weights: wr[k][s] = W'[k][c0 + 4q + s][n0 + li]
-  constexpr int KLO = 13;
-  auto load_w = [&](bool hi) {  // taps k < KLO, or k >= KLO
-    const int n = n0 + li, c = c0 + 4 * q;
-    const bool ok = n < nn && c < kk;
-#pragma unroll
-    for (int k = 0; k < K3; ++k) {
-      if ((k >= KLO) != hi) continue;
-      v4f v = {0.f, 0.f, 0.f, 0.f};
-      if (ok) {
-        if constexpr (FLIP) {
-          v = *reinterpret_cast<const v4f*>(w + ((int64_t)(K3 - 1 - k) * nn + n) * kk + c);
-        } else {
-#pragma unroll
-          for (int s = 0; s < 4; ++s) v[s] = w[((int64_t)k * kk + c + s) * nn + n];
-        }
-      }
-      wr[k] = v;
-    }
-  };
-
-  // the rows of tap k+1 are read before the MFMAs of tap k
-  auto compute = [&](const v4f* buf, v4f (&acc)[RB]) {
-    v4f b[2][RB];
-#pragma unroll
-    for (int r = 0; r < RB; ++r) b[0][r] = buf[aoff[0] + 2 * r * GSTR];
-#pragma unroll
-    for (int k = 0; k < K3; ++k) {
-      const int cu = k & 1, nx2 = cu ^ 1;
-      if (k + 1 < K3) {
-#pragma unroll
-        for (int r = 0; r < RB; ++r)
-          b[nx2][r] = buf[aoff[(k + 1) % 9] + ((k + 1) / 9) * XSTR + 2 * r * GSTR];
-      }
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int s = 0; s < 4; ++s)
-#pragma unroll
-        for (int r = 0; r < RB; ++r) acc[r] = mfma4(wr[k][s], b[cu][r][s], acc[r]);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  };
-  // one row block rb of the tile (the partial last tile), into acc
-  auto compute1 = [&](const v4f* buf, int rb, v4f& acc) {
-    const v4f* bb = buf + 2 * (rb - wm * RB) * GSTR;
-    v4f b[2];
-    b[0] = bb[aoff[0]];
-#pragma unroll
-    for (int k = 0; k < K3; ++k) {
-      const int cu = k & 1, nx2 = cu ^ 1;
-      if (k + 1 < K3) b[nx2] = bb[aoff[(k + 1) % 9] + ((k + 1) / 9) * XSTR];
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int s = 0; s < 4; ++s) acc = mfma4(wr[k][s], b[cu][s], acc);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  };
-  const int64_t nrows = 8 * ngroups;
-  const bool split = gridDim.z > 1;
-  float* dst = split ? part + (int64_t)blockIdx.z * nrows * nn : out;
-  // accumulator j of lane l: output channel 4(l/16) + j, row l % 16; stored
-  // after store_order: lane l writes row l/4, channels 4(l%4)..
-  const int64_t rowe = 8 * g1;  // rows past the range are not stored
-  // pr: the pooled forward's output row of this lane's group
-  auto store_rb = [&](int t, int rb, const v4f& acc, int32_t pr) {
-    if constexpr (POOL) {
-      // through the wave's LDS area: lane o < 32 pools group o/16 of the
-      // row block in channel n0 + o%16
-      v4f v = acc;
-      if (relu) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) v[j] = fmaxf(v[j], 0.f);
-      }
-      float* ps = &PS[wave][0];
-      oc::pool_put(ps, v, lane);
-      uint32_t sw;
-      const float m = oc::pool_scan(ps, lane, sw);
-      const int c = n0 + (lane & 15);
-      const int64_t g = g0 + (int64_t)t * GPB + 2 * rb + ((lane >> 4) & 1);
-      if (lane < 32 && c < nn && g < g1) {
-        out[(int64_t)pr * nn + c] = m;
-        psw[g * nn + c] = (uint8_t)sw;
-      }
-      return;
-    }
-    const int n = n0 + 4 * (lane & 3);
-    const int64_t row = 8 * (g0 + (int64_t)t * GPB) + 16 * rb + (lane >> 2);
-    const v4f sv = store_order(acc, lane);
-    if (n < nn && row < rowe) {
-      v4f v = sv;
-      if (!split && relu) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) v[j] = fmaxf(v[j], 0.f);
-      }
-      *reinterpret_cast<v4f*>(dst + row * nn + n) = v;
-    }
-  };
-  auto epilogue = [&](int t, v4f (&acc)[RB]) {
-#pragma unroll
-    for (int r = 0; r < RB; ++r) {
-      store_rb(t, wm * RB + r, acc[r], POOL ? prq[r] : 0);
-      acc[r] = v4f{0.f, 0.f, 0.f, 0.f};
-    }
-  };
-  // tile t: wait for its loads everywhere (and for tile t-1's reads), write
-  // tile t-1, start tile t+1's loads, multiply tile t
-  auto step = [&](int t, const v4f* cur, v4f* nxt, v4f (&accc)[RB], v4f (&accp)[RB],
-                  bool first) {
-    vm_wait0();  // this wave's loads into cur have landed
-    __syncthreads();
-    if (t > 0) epilogue(t - 1, accp);
-    load_pr(t);  // lands during tile t's MFMAs
-#pragma unroll
-    for (int i = 0; i < GPB; ++i) nbc[i] = nbn[i];
-    okc = okn;
-    if (t + 1 < T) {
-      load_nb(t + 2, nbn, okn);
-      dma(nxt);
-    }
-    if (first) load_w(true);  // the later taps' weights land during tile 0
-    __builtin_amdgcn_sched_barrier(0);
-    compute(cur, accc);
-  };
-
-  // the first tile's neighbour entries, the first KLO taps' weights and the
-  // first tile's rows are in flight together; the other taps' weights are
-  // loaded at the start of tile 0 and waited for tap by tap
-  load_nb(0, nbc, okc);
-  load_w(false);
-  dma(X0);
-  load_nb(1, nbn, okn);
-
-  // tiles 0 .. T-2 (tile 0 apart, with the rest of the weights), then the
-  // last one (in X0 when T-1 is even)
-  if (T > 1) step(0, X0, X1, acc0, acc1, true);
-  for (int t = 1; t + 1 < T; t += 2) {
-    step(t, X1, X0, acc1, acc0, false);
-    if (t + 2 < T) step(t + 1, X0, X1, acc0, acc1, false);
-  }
-  const bool last0 = (T - 1) % 2 == 0;
-  vm_wait0();
-  __syncthreads();
-  if (T > 1) {
-    if (last0)
-      epilogue(T - 2, acc1);
-    else
-      epilogue(T - 2, acc0);
-  }
-  if (T == 1) load_w(true);
-  // live row blocks of the last tile, rb = wm + WM i
-  const int rbl = (int)((g1 - g0 - (int64_t)(T - 1) * GPB + 1) / 2);
-  for (int rb = wm; rb < rbl; rb += WM) {
-    int32_t pr = 0;
-    if constexpr (POOL) {
-      const int64_t g = g0 + (int64_t)(T - 1) * GPB + 2 * rb + ((lane >> 4) & 1);
-      pr = g < g1 ? prow[g] : -1;
-    }
-    v4f a = v4f{0.f, 0.f, 0.f, 0.f};
-    compute1(last0 ? X0 : X1, rb, a);
-    store_rb(T - 1, rb, a, pr);
   }
 }
 
@@ -1542,8 +1246,7 @@ void sum_parts(const float* part, int np, int64_t n, float* out, hipStream_t s) 
 struct TileCfg {
   int V, MR, NR, WM, splits, cps;
   bool VEC;
-  bool v2;  // k_conv_tile3: K = 3, 16-channel chunks, one chunk per split
-  int gpb;  // k_conv_tile3: sibling groups per tile
+  bool v2;  // k_conv_sp3: K = 3, 16-channel chunks, one chunk per split
 };
 
 // Workgroup tile and split of the reduction for a stride-1 layer of G groups
@@ -1553,32 +1256,11 @@ TileCfg pick_tile(int K, int64_t G, int kk, int nn) {
   c.VEC = kk % 4 == 0 && nn % 4 == 0;
   c.v2 = K == 3 && c.VEC && kk >= 16;
   if (c.v2) {
-    c.V = 4, c.MR = 1, c.WM = 4;
-    c.NR = nn <= 16 ? 1 : nn <= 32 ? 2 : 4;  // column blocks per workgroup (WN)
-    c.cps = 1;
-    c.splits = (int)oc::cdiv(kk, 16);
-    // tile size: the least time for the longest range of groups (two
-    // workgroups per CU), counting a wave's row blocks plus a fixed cost per
-    // tile (barrier, loads, stores) of about 3/4 of a row block
-    const int64_t slots = 2 * (int64_t)oc::cu_count();
-    const int64_t gyz = oc::cdiv(nn, 16 * c.NR) * c.splits;
-    const int64_t ng = oc::cdiv(G, std::max<int64_t>(1, slots / gyz));
-    const int wm = WAVES / c.NR;
-    double best = 1e30;
-    c.gpb = 8;
-    for (int gpb = 8; gpb >= 2; gpb /= 2) {
-      if (gpb / 2 < wm) break;  // a row block for every wave
-      const int rb = gpb / 2 / wm;
-      const int64_t full = ng / gpb, tail = ng - full * gpb;
-      const double cost = full * (rb + 0.75) +
-                          (tail > 0 ? (double)oc::cdiv(oc::cdiv(tail, 2), wm) + 0.75 : 0.0);
-      if (cost < best - 1e-9) best = cost, c.gpb = gpb;
-    }
+    c.splits = oc::sp3_pick(G, kk, nn).splits;
     return c;
   }
-  c.V = (K == 3 && kk >= 16 && c.VEC) ? 4 : 1;
-  c.WM = 4;
-  if (c.V == 1 && K == 3) {
+  c.V = 1, c.WM = 4;
+  if (K == 3) {
     c.MR = 2, c.NR = 1;  // 128 x 16
   } else {
     c.MR = 1, c.NR = nn <= 16 ? 1 : 2;  // 64 x 16 or 64 x 32
@@ -1621,73 +1303,18 @@ void launch_tile(const oc_octree* t, int l, const TileCfg& c, const float* x, in
   }
 }
 
-// Destination of a pooled forward (conv + ReLU + 2x2x2 max-pool): the
-// pooled rows of depth l-1 and the switches.
-struct PoolOut {
-  float* y;
-  uint8_t* sw;
-};
-
-template <int NR, int GPB, bool FLIP>
-void launch_tile2(const oc_octree* t, int l, const TileCfg& c, const float* x, int kk,
-                  const float* w, int nn, float* out, int relu, float* part, hipStream_t s,
-                  const PoolOut* po = nullptr, const RouteOut* ro = nullptr) {
-  const auto plain = k_conv_tile3<NR, GPB, FLIP, false>;
-  const auto pooled = k_conv_tile3<NR, GPB, FLIP, true>;
-  const bool fuse = !FLIP && po && c.splits == 1;
-  const auto kernel = fuse ? pooled : plain;
-  static const int occ = [&] {
-    int n = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, plain, TB, 0) != hipSuccess || n < 1)
-      n = 1;
-    return n;
-  }();
-  const int64_t G = t->M[l - 1];
-  const int64_t gy = oc::cdiv(nn, 16 * NR), gyz = gy * c.splits;
-  // one resident workgroup per slot, each over a contiguous range of groups
-  int64_t px = std::min<int64_t>(G, std::max<int64_t>(1, (int64_t)oc::cu_count() * occ / gyz));
-  if (px >= 8) px -= px % 8;
-  dim3 grid((unsigned)px, (unsigned)gy, (unsigned)c.splits);
-  if (fuse) {
-    oc::launch_main(kernel, grid, dim3(TB), s, (const int32_t*)t->nbr[l], G, x, kk, w, nn, po->y,
-                    relu, part, (const int32_t*)t->rows[l - 1], (const int32_t*)t->labels[l - 1],
-                    t->N[l - 1], po->sw);
-    return;
-  }
-  oc::launch_main(kernel, grid, dim3(TB), s, (const int32_t*)t->nbr[l], G, x, kk, w, nn, out,
-                  relu, part, (const int32_t*)nullptr, (const int32_t*)nullptr, (int64_t)0,
-                  (uint8_t*)nullptr);
-  if (ro) {  // input gradient routed on (relu is 0)
-    route_parts(t, l, c.splits > 1 ? part : out, c.splits, nn, *ro, s);
-    return;
-  }
-  if (c.splits > 1) {
-    if (po) {
-      const int cv = nn / 4;
-      const int64_t npar = t->N[l - 1];
-      oc::launch(k_sum_split_pool, dim3((unsigned)oc::cdiv(npar * cv, TB)), dim3(TB), 0, s,
-                 (const float*)part, c.splits, t->N[l] * (int64_t)nn,
-                 (const int32_t*)t->labels[l - 1], (const int32_t*)t->rows[l - 1], npar,
-                 t->M[l - 1], cv, relu, po->y, po->sw);
-    } else {
-      sum_split(part, c.splits, t->N[l] * (int64_t)nn, out, relu, s);
-    }
-  }
-}
-
 template <bool FLIP>
 void dispatch_tile(const oc_octree* t, int l, int K, const float* x, int kk, const float* w,
                    int nn, float* out, int relu, float* part, hipStream_t s,
                    const RouteOut* ro = nullptr) {
   const TileCfg c = pick_tile(K, t->M[l - 1], kk, nn);
   if (c.v2) {
-#define OC_T3(NR_, GPB_)                                                                 \
-  if (c.NR == NR_ && c.gpb == GPB_) {                                                    \
-    launch_tile2<NR_, GPB_, FLIP>(t, l, c, x, kk, w, nn, out, relu, part, s, nullptr, ro); \
-    return;                                                                              \
-  }
-    OC_T3(1, 8) OC_T3(2, 8) OC_T3(2, 4) OC_T3(4, 8) OC_T3(4, 4) OC_T3(4, 2)
-#undef OC_T3
+    const oc::Sp3Cfg sc = oc::sp3_pick(t->M[l - 1], kk, nn);
+    oc::sp3_launch(t, l, sc, FLIP, x, kk, w, nn, out, relu, part, nullptr, s);
+    if (ro)  // input gradient routed on (relu is 0)
+      route_parts(t, l, sc.splits > 1 ? part : out, sc.splits, nn, *ro, s);
+    else if (sc.splits > 1)
+      sum_split(part, sc.splits, t->N[l] * (int64_t)nn, out, relu, s);
     return;
   }
 #define OC_TILE(K_, V_, MR_, NR_, WM_, VEC_)                                                    \
@@ -1695,7 +1322,6 @@ void dispatch_tile(const oc_octree* t, int l, int K, const float* x, int kk, con
     launch_tile<K_, V_, MR_, NR_, WM_, FLIP, VEC_>(t, l, c, x, kk, w, nn, out, relu, part, s, ro); \
     return;                                                                                     \
   }
-  OC_TILE(3, 4, 1, 1, 4, true) OC_TILE(3, 4, 1, 2, 4, true)
   OC_TILE(3, 1, 2, 1, 4, true) OC_TILE(3, 1, 2, 1, 4, false)
   OC_TILE(5, 1, 1, 1, 4, true) OC_TILE(5, 1, 1, 1, 4, false)
   OC_TILE(5, 1, 1, 2, 4, true) OC_TILE(5, 1, 1, 2, 4, false)
@@ -1883,8 +1509,7 @@ void conv_s1_kernel_name(const oc_octree* t, int l, int K, int cin, int cout, in
   const int kk = pass == 0 ? cin : cout, nn = pass == 0 ? cout : cin;
   const TileCfg c = pick_tile(K, t->M[l - 1], kk, nn);
   if (c.v2) {
-    snprintf(buf, n, "k_conv_tile3<%d, %d, %s, %s>", c.NR, c.gpb, pass == 0 ? "false" : "true",
-             pooled && c.splits == 1 ? "true" : "false");
+    oc::sp3_name(oc::sp3_pick(t->M[l - 1], kk, nn), pass == 1, pooled, buf, n);
     return;
   }
   snprintf(buf, n, "k_conv_tile<%d, %d, %d, %d, %d, %s, %s>", K, c.V, c.MR, c.NR, c.WM,
@@ -1929,16 +1554,17 @@ void conv_s1_pool_fwd_f32(const oc_octree* t, int l, int K, const float* x, int 
     conv_cin_pool_fwd(t, l, x, cin, w, cout, yp, sw, relu, s);
     return;
   }
-  const TileCfg c = pick_tile(K, t->M[l - 1], cin, cout);
-  const PoolOut po{yp, sw};
-#define OC_T3(NR_, GPB_)                                                              \
-  if (c.NR == NR_ && c.gpb == GPB_) {                                                 \
-    launch_tile2<NR_, GPB_, false>(t, l, c, x, cin, w, cout, nullptr, relu, ws, s, &po); \
-    return;                                                                           \
+  const oc::Sp3Cfg c = oc::sp3_pick(t->M[l - 1], cin, cout);
+  const oc::Sp3Pool po{yp, sw};
+  oc::sp3_launch(t, l, c, false, x, cin, w, cout, nullptr, relu, ws, &po, s);
+  if (c.splits > 1) {
+    const int cv = cout / 4;
+    const int64_t npar = t->N[l - 1];
+    oc::launch(k_sum_split_pool, dim3((unsigned)oc::cdiv(npar * cv, TB)), dim3(TB), 0, s,
+               (const float*)ws, c.splits, t->N[l] * (int64_t)cout,
+               (const int32_t*)t->labels[l - 1], (const int32_t*)t->rows[l - 1], npar,
+               t->M[l - 1], cv, relu, yp, sw);
   }
-  OC_T3(1, 8) OC_T3(2, 8) OC_T3(2, 4) OC_T3(4, 8) OC_T3(4, 4) OC_T3(4, 2)
-#undef OC_T3
-  oc::set_error("no pooled kernel for cin=%d cout=%d", cin, cout);
 }
 
 void conv_s1_bwd_data_f32(const oc_octree* t, int l, int K, const float* dy, int cout,

@@ -95,6 +95,102 @@ def test_conv_small_fp32(seed, B, n, depth, K, stride, cin, cout, relu):
     assert torch.equal(dw.view(torch.int32), dw2.view(torch.int32))
 
 
+SPLIT_SMALL = [  # seed, B, n, depth, cin, cout: fp32 products from bf16 parts
+    (201, 1, 1, 3, 16, 16),     # a handful of groups, one tile
+    (202, 2, 300, 4, 16, 4),    # fewer output channels than a block
+    (203, 2, 500, 4, 20, 36),   # ragged reduction chunk and column block
+    (204, 3, 700, 5, 28, 64),   # half a channel octet at the end
+    (205, 1, 900, 5, 32, 80),   # two column blocks of 64
+    (206, 2, 900, 5, 48, 32),   # three chunks, 32-column tiles
+    (207, 9, 40, 4, 64, 132),   # many shapes, three column blocks, a ragged one
+]
+
+
+@pytest.mark.parametrize("seed,B,n,depth,cin,cout", SPLIT_SMALL)
+def test_conv_split_parts(seed, B, n, depth, cin, cout):
+    """K = 3 fp32 layers whose products are formed from bf16 parts: both passes
+    against the oracle.  One product's parts leave out less than 2^-24 of it, so
+    the error stays that of fp32 sums: below 5e-7 of the result's norm (2e-7
+    seen) where a single bf16 part would give 2e-3."""
+    oc = _oc()
+    print(f"[split] seed={seed} B={B} d={depth} {cin}->{cout}", flush=True)
+    ref, tree = _trees(*synth.random_cloud(seed, B, n, "union"), depth)
+    rng = np.random.default_rng(seed)
+    x = rng.standard_normal((ref.num(depth), cin)).astype(np.float32)
+    x *= np.exp2(rng.integers(-20, 20, (ref.num(depth), 1))).astype(np.float32)
+    w = (rng.standard_normal((27, cin, cout)) / np.sqrt(27 * cin)).astype(np.float32)
+    dy = rng.standard_normal((ref.num(depth), cout)).astype(np.float32)
+    nb = ref.neighbors(depth, 3)
+    y = oc.oc_conv_fwd(tree, depth, 3, 1, _cuda(x), _cuda(w)).cpu().numpy()
+    yr = oracle.conv_fwd(nb, x, w)
+    # rows of very different size: per row, against what its terms add up to
+    size = np.sqrt(oracle.conv_fwd(nb, x.astype(np.float64) ** 2, w.astype(np.float64) ** 2))
+    assert np.linalg.norm((y - yr) / size) <= 5e-7 * np.linalg.norm(yr / size)
+    dx, dw = oc.oc_conv_bwd(tree, depth, 3, 1, _cuda(x), _cuda(w), _cuda(dy))
+    dxr = oracle.conv_bwd_data(nb, dy, w, ref.num(depth))
+    assert_f32_close(dx.cpu().numpy(), dxr, "dx")
+    assert np.linalg.norm(dx.cpu().numpy() - dxr) <= 5e-7 * np.linalg.norm(dxr)
+    dwr = oracle.conv_bwd_weight(nb, x, dy, 27)
+    assert np.linalg.norm(dw.cpu().numpy() - dwr) <= 1e-6 * np.linalg.norm(dwr)
+
+
+@pytest.mark.parametrize("cin,cout,where", [(16, 16, "x"), (20, 64, "x"), (32, 32, "w")])
+def test_conv_split_not_finite(cin, cout, where):
+    """Infinities, NaN and values whose bf16 rounding is infinite have no finite
+    parts; their results are those of plain fp32 products, and no other result
+    changes."""
+    oc = _oc()
+    ref, tree = _trees(*synth.random_cloud(211, 2, 500, "union"), 4)
+    l, rng = 4, np.random.default_rng(cout)
+    x = rng.standard_normal((ref.num(l), cin)).astype(np.float32)
+    w = (rng.standard_normal((27, cin, cout)) / 8).astype(np.float32)
+    dy = rng.standard_normal((ref.num(l), cout)).astype(np.float32)
+    w[3, 0, :] = 1.0  # exact in bf16: its other parts are zero
+    a = x if where == "x" else w.reshape(-1, cout)
+    for i, v in enumerate((np.inf, -np.inf, np.nan, 3.4e38, -3.4e38)):
+        a[(7 + 41 * i) % len(a), i] = v
+    dyi = dy.copy()
+    if where == "x":  # with an overflowing weight's product it would make NaN in fp32
+        dyi[5, 1] = np.inf
+    # absent neighbours read as zero, times an infinity NaN
+    nb = ref.neighbors(l, 3)
+    pad = lambda v: np.concatenate([v, np.zeros((1, v.shape[1]))]).astype(np.float64)  # noqa: E731
+    w64, col = w.astype(np.float64), [pad(x)[nb[:, k]] for k in range(27)]
+    with np.errstate(all="ignore"):
+        yr = sum(col[k] @ w64[k] for k in range(27))
+        dxr = sum(pad(dyi)[nb[:, 26 - k]] @ w64[k].T for k in range(27))
+        dwr = np.stack([c.T @ dy.astype(np.float64) for c in col])
+        y = oc.oc_conv_fwd(tree, l, 3, 1, _cuda(x), _cuda(w))
+        dx, _ = oc.oc_conv_bwd(tree, l, 3, 1, _cuda(x), _cuda(w), _cuda(dyi), need_dw=False)
+        _, dw = oc.oc_conv_bwd(tree, l, 3, 1, _cuda(x), _cuda(w), _cuda(dy), need_dx=False)
+        pairs = [("y", y, yr), ("dx", dx, dxr), ("dw", dw, dwr)]
+        for tag, g, r in pairs:
+            g, r = g.cpu().numpy(), r.astype(np.float32)  # overflows as fp32 does
+            assert np.array_equal(np.isnan(g), np.isnan(r)), tag
+            assert np.array_equal(np.isposinf(g), np.isposinf(r)), tag
+            assert np.array_equal(np.isneginf(g), np.isneginf(r)), tag
+            ok = np.isfinite(r)
+            assert np.all(np.abs(g[ok] - r[ok]) <= 1e-4 * np.abs(r[ok]) + 1e-4), tag
+
+
+def test_conv_split_4gib():
+    """An input of 4 GiB and more (64-bit row addresses): only the last chunk's
+    channels are not zero, so the result is that of the small layer they make,
+    bit for bit."""
+    oc = _oc()
+    pts, nrm, offs = synth.make_points("deep_d8")
+    tree = oc.oc_build(torch.as_tensor(pts).cuda(), torch.as_tensor(nrm).cuda(), offs, 8, 2)
+    n = tree.num(8)
+    cin = -(-(1 << 30) // n // 16) * 16 + 16
+    x = torch.zeros((n, cin), device="cuda")
+    assert x.numel() * 4 >= 1 << 32
+    x[:, -16:] = torch.randn((n, 16), device="cuda")
+    w = torch.randn((27, cin, 4), device="cuda")
+    y = oc.oc_conv_fwd(tree, 8, 3, 1, x, w)
+    ys = oc.oc_conv_fwd(tree, 8, 3, 1, x[:, -16:].contiguous(), w[:, -16:].contiguous())
+    assert torch.equal(y, ys)
+
+
 SR_SMALL = [  # seed, B, n, depth, stride, cin, cout, relu, bf16
     (101, 2, 400, 4, 4, 5, 7, False, False),
     (102, 3, 600, 5, 4, 16, 32, True, False),
