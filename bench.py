@@ -346,7 +346,7 @@ TRACE_CLASSES = (
                "__amd_rocclr_copyBuffer")),
     ("pool", ("k_pool_fwd", "k_route_down", "k_route_up", "k_gpool_", "k_route_parts")),
     ("conv_main", ("k_conv_", "k_cin_", "k_sr_mm<", "k_sr_dw<")),
-    ("conv_helper", ("k_sum_", "k_relu_mask", "k_bf_", "k_bf16_to_f32", "k_sr_", "k_dc_",
+    ("conv_helper", ("k_sum_", "k_relu_mask", "k_bf_", "k_sp_", "k_bf16_to_f32", "k_sr_", "k_dc_",
                      "k_fill_u32")),
 )
 

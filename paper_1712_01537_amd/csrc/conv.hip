@@ -177,14 +177,13 @@ size_t bwd_pool_ws_bytes(const oc_octree* t, int32_t l, const ConvShape& sh, int
 size_t bwd_ws_bytes(const oc_octree* t, int32_t l, const ConvShape& sh, oc_dtype dt, int cin,
                     int cout) {
   if (sh.units == 0) return 0;
-  const size_t entries = (size_t)sh.K3 * cin * cout;
   if (bf16_native(sh, dt, cin, cout)) return oc::conv_bf16_bwd_ws(t, l, sh.K, cin, cout);
   if (sh.stride == 1) {
     // (bf16: the widened w and x,) the ReLU-masked upstream gradient, then
     // the input gradient's and the weight gradient's partial sums: the same
     // bytes serve both in stream order
     const size_t a = oc::conv_s1_tile_ws(t, l, sh.K, cout, cin);
-    const size_t b = oc::conv_s1_dw_parts(t, l, sh.K, cin, cout) * entries * sizeof(float);
+    const size_t b = oc::conv_s1_dw_ws(t, l, sh.K, cin, cout);
     const size_t wide = dt == OC_F32 ? 0 : w32_bytes(sh, cin, cout) + x32_bytes(sh, cin);
     return wide + mask_ws_bytes(sh, cout) + std::max(a, b);
   }

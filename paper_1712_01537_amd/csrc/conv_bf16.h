@@ -40,4 +40,25 @@ void conv_bf16_bwd(const oc_octree* t, int l, int K, const uint16_t* x, int cin,
 // y[e] = bf16(x[e]) for e < n, round to nearest even (NaN stays NaN).
 void round_bf16(const float* x, int64_t n, uint16_t* y, hipStream_t s);
 
+// K = 5 fp32 convolution on the bf16 kernels, each fp32 operand in three bf16
+// parts (conv_bf16.hip).  sp5_fwd computes the forward (flip: the input
+// gradient, kk = cout, nn = cin) and returns a flag in ws (sp5_fwd_ws bytes)
+// that the GPU sets when an output is infinite or NaN: the split has no such
+// values, so the caller then computes the layer again with the fp32 kernel,
+// gated on the flag.  out 16-byte aligned.  sp5_dw: the same for the weight
+// gradient (ws: sp5_dw_ws bytes, dw 16-byte aligned); sp5_sum_gated adds the
+// fp32 kernel's partial sums when the flag is set.
+bool sp5_fwd_ok(const oc_octree* t, int l, int K, int kk, int nn);
+size_t sp5_fwd_ws(const oc_octree* t, int l, int kk, int nn);
+uint32_t* sp5_fwd(const oc_octree* t, int l, bool flip, const float* x, int kk, const float* w,
+                  int nn, float* out, int relu, void* ws, hipStream_t s);
+void sp5_fwd_name(bool flip, char* buf, size_t n);
+bool sp5_dw_ok(const oc_octree* t, int l, int K, int cin, int cout);
+size_t sp5_dw_ws(const oc_octree* t, int l, int cin, int cout);
+uint32_t* sp5_dw(const oc_octree* t, int l, const float* x, int cin, const float* dy, int cout,
+                 float* dw, void* ws, hipStream_t s);
+void sp5_sum_gated(const float* part, int nparts, int64_t n, float* out, const uint32_t* gate,
+                   hipStream_t s);
+void sp5_dw_name(char* buf, size_t n);
+
 }  // namespace oc

@@ -40,6 +40,7 @@
 // the four rows of a transposing load (weight gradient), then fall on
 // distinct banks.
 #include "conv_bf16.h"
+#include "split3.h"
 
 #include <algorithm>
 #include <utility>
@@ -289,13 +290,92 @@ __global__ __launch_bounds__(TB) void k_bf_cvt_g(const float* __restrict__ in,
 }
 
 // out[e] = sum_{r < nparts} part[r][e] in the order r = 0, 1, ... (n % 4 == 0).
+// gate != NULL: only when *gate is set; bad != NULL: *bad = 1 when a sum is
+// infinite or NaN.
 __global__ __launch_bounds__(TB) void k_bf_sum(const float* __restrict__ part, int nparts,
-                                               int64_t n, float* __restrict__ out) {
+                                               int64_t n, float* __restrict__ out,
+                                               const uint32_t* __restrict__ gate, uint32_t* bad) {
+  if (gate && *gate == 0) return;
   const int64_t e = 4 * ((int64_t)blockIdx.x * TB + threadIdx.x);
   if (e >= n) return;
   v4f s = {0.f, 0.f, 0.f, 0.f};
   for (int r = 0; r < nparts; ++r) s += *reinterpret_cast<const v4f*>(part + r * n + e);
   *reinterpret_cast<v4f*>(out + e) = s;
+  if (bad && oc::s3_bad(s)) *bad = 1;
+}
+
+// ---------------------------------------------------------------------------
+// fp32 operands as three bf16 parts (split3.h), for the K = 5 kernels below:
+// an fp32 product is six bf16 products, so an fp32 reduction over kk channels
+// is a bf16 one over 6 kk "virtual" channels, product p taking part
+// x_part(p) of x and w_part(p) of w, the smallest products first.
+__host__ __device__ constexpr int x_part(int p) { return (0x052 >> (2 * p)) & 3; }  // 2 0 1 1 0 0
+__host__ __device__ constexpr int w_part(int p) { return (0x118 >> (2 * p)) & 3; }  // 0 2 1 0 1 0
+
+__device__ __forceinline__ oc::Split8 load_split8(const oc::SplitK& k, const float* p, int vec) {
+  v4f a, b;
+  if (vec) {
+    a = *reinterpret_cast<const v4f*>(p);
+    b = *reinterpret_cast<const v4f*>(p + 4);
+  } else {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) a[j] = p[j], b[j] = p[j + 4];
+  }
+  return oc::s3_split8(k, a, b);
+}
+
+// Rows [n8 * 8 / C][C] of x as [row][3 C]: the three parts of a row one after
+// the other (C % 8 == 0).  Eight channels per thread; bound by memory (4 bytes
+// read, 6 written a value).  vec: x is 16-byte aligned.
+__global__ __launch_bounds__(TB) void k_sp_rows(const float* __restrict__ x, int64_t n8, int C8,
+                                                int vec, uint16_t* __restrict__ x3) {
+  const int64_t i = (int64_t)blockIdx.x * TB + threadIdx.x;
+  if (i >= n8) return;
+  const int64_t row = i / C8;
+  const int o = (int)(i - row * C8);
+  const oc::Split8 sp = load_split8(oc::s3_consts(), x + 8 * i, vec);
+  v4u* d = reinterpret_cast<v4u*>(x3) + 3 * row * C8 + o;
+#pragma unroll
+  for (int p = 0; p < 3; ++p) d[p * C8] = sp.p[p];
+}
+
+// The weights' parts in the order of k_bf_wprep over the virtual octets
+// p KO + o (KO = kk / 8): wp[p KO + o][t][n][8].  Also clears *flag.
+__global__ __launch_bounds__(TB) void k_sp_wprep(const float* __restrict__ w, int K3, int kk,
+                                                 int nn, int flip, uint16_t* __restrict__ wp,
+                                                 uint32_t* flag) {
+  const int64_t i = (int64_t)blockIdx.x * TB + threadIdx.x, per = (int64_t)(kk / 8) * K3 * nn;
+  if (i == 0) *flag = 0;
+  if (i >= per) return;
+  const int n = (int)(i % nn);
+  const int t = (int)(i / nn % K3), c = 8 * (int)(i / nn / K3);
+  v4f v[2];
+#pragma unroll
+  for (int e = 0; e < 8; ++e)
+    v[e / 4][e % 4] = flip ? w[((int64_t)(K3 - 1 - t) * nn + n) * kk + c + e]
+                           : w[((int64_t)t * kk + c + e) * nn + n];
+  const oc::Split8 sp = oc::s3_split8(oc::s3_consts(), v[0], v[1]);
+#pragma unroll
+  for (int p = 0; p < 6; ++p) reinterpret_cast<v4u*>(wp)[p * per + i] = sp.p[w_part(p)];
+}
+
+// The parts of dY in the sibling-group layout of k_bf_cvt_g:
+// outg[part][g][c][8].  One (group, column) per thread, coalesced over the
+// columns.  Also clears *flag.
+__global__ __launch_bounds__(TB) void k_sp_cvt_g(const float* __restrict__ in, int64_t ngroups,
+                                                 int C, uint16_t* __restrict__ outg,
+                                                 uint32_t* flag) {
+  const int64_t i = (int64_t)blockIdx.x * TB + threadIdx.x, n = ngroups * C;
+  if (i == 0) *flag = 0;
+  if (i >= n) return;
+  const int64_t g = i / C;
+  const float* p = in + 8 * g * C + (i - g * C);
+  v4f v[2];
+#pragma unroll
+  for (int j = 0; j < 8; ++j) v[j / 4][j % 4] = p[(int64_t)j * C];
+  const oc::Split8 sp = oc::s3_split8(oc::s3_consts(), v[0], v[1]);
+#pragma unroll
+  for (int k = 0; k < 3; ++k) reinterpret_cast<v4u*>(outg)[k * n + i] = sp.p[k];
 }
 
 // ---------------------------------------------------------------------------
@@ -581,12 +661,16 @@ struct BfwShape {
   }
 };
 
-template <int K, int HC, bool FLIP, int GT_, int NW_>
+// SP: fp32 operands in three bf16 parts.  x is [8 ngroups][3 kk], wp as
+// k_sp_wprep writes it, and the workgroup walks all chunks of the 6 kk virtual
+// channels, its sums staying in registers; *bad = 1 when an output is infinite
+// or NaN.
+template <int K, int HC, bool FLIP, int GT_, int NW_, bool SP>
 __global__ __launch_bounds__(NW_ * 64, 8 / NW_) void k_conv_bfw(const int32_t* __restrict__ nbr, int64_t ngroups,
                                                    const uint16_t* __restrict__ x, int kk,
                                                    const uint16_t* __restrict__ wp, int nn,
                                                    int chunk, float* __restrict__ out, int acc_in,
-                                                   int relu) {
+                                                   int relu, uint32_t* bad) {
   using B = BfwShape<K, HC, GT_, NW_>;
   constexpr int R = B::R, S = B::S, S2 = B::S2, K2 = B::K2, K3 = B::K3;
   constexpr int GT = B::GT, NW = B::NW, NRB = B::NRB, SLAB = B::SLAB, NB = B::NB;
@@ -611,7 +695,16 @@ __global__ __launch_bounds__(NW_ * 64, 8 / NW_) void k_conv_bfw(const int32_t* _
   const int tile = xcd * tper + (xcd < (ntiles & 7) ? xcd : (ntiles & 7)) + ((int)blockIdx.x >> 3);
   const int64_t g0 = (int64_t)tile * GT;
   const int n0 = blockIdx.y * 64;
-  const int ob = 8 * chunk;
+  const int rs = SP ? 3 * kk : kk;  // row length of x
+  int ob = 8 * chunk;               // first (virtual) octet of the chunk
+  // octet of a row of x that half h of the chunk starts at (kk % 32 == 0: a
+  // half never spans two products)
+  auto x_oct = [&](int h) {
+    const int v = ob + 4 * h;
+    if constexpr (!SP) return v;
+    const int ko = kk >> 3, p = v / ko;
+    return v + (x_part(p) - p) * ko;
+  };
   if (tid < GT * 27 + 27)
     nbs[tid] = tid < GT * 27 && g0 + tid / 27 < ngroups ? nbr[27 * g0 + tid] : -1;
 
@@ -621,10 +714,10 @@ __global__ __launch_bounds__(NW_ * 64, 8 / NW_) void k_conv_bfw(const int32_t* _
   // tile: nbi[k] = the lane's neighbour entry without the x-cell, eb[k] =
   // the byte offset in the row block of its child's y, z bits and of its
   // 16-byte piece before the slab's swizzle.  The piece is
-  // ((s & 3) ^ (py & 1)) ^ 2 (j & 1) of octet block ob + 4h (the launcher
+  // ((s & 3) ^ (py & 1)) ^ 2 (j & 1) of octet block x_oct(h) (the launcher
   // guarantees every such octet exists), and an absent row reads zeros
   // through an offset past the end of x.
-  const sv4 xr = buf_rsrc(x, (uint32_t)(8 * ngroups * kk * 2));
+  const sv4 xr = buf_rsrc(x, (uint32_t)(8 * ngroups * rs * 2));
   int nbi[DC];
   uint32_t eb[DC];
 #pragma unroll
@@ -635,7 +728,7 @@ __global__ __launch_bounds__(NW_ * 64, 8 / NW_) void k_conv_bfw(const int32_t* _
     const int py = p / S, pz = p - py * S;
     const int uy = py - R, uz = pz - R;
     nbi[k] = i < NDMA ? 27 * g + ((uy >> 1) + 1) * 3 + ((uz >> 1) + 1) : GT * 27;
-    eb[k] = 2u * (uint32_t)((2 * (uy & 1) + (uz & 1)) * kk + 8 * (ob + ((s & 3) ^ (py & 1))));
+    eb[k] = 2u * (uint32_t)((2 * (uy & 1) + (uz & 1)) * rs + 8 * ((s & 3) ^ (py & 1)));
   }
   __syncthreads();
 
@@ -645,7 +738,7 @@ __global__ __launch_bounds__(NW_ * 64, 8 / NW_) void k_conv_bfw(const int32_t* _
     const int ux = j - R, xcell = (ux >> 1) + 1;
     v4u* buf = lds + (sl % NB) * SLAB;
     // the slab's constant (the child's x bit and the half) and swizzle term
-    const uint32_t cb = 2u * (uint32_t)(4 * (ux & 1) * kk + 32 * h), xo = 32u * (uint32_t)(j & 1);
+    const uint32_t cb = 2u * (uint32_t)(4 * (ux & 1) * rs + 8 * x_oct(h)), xo = 32u * (uint32_t)(j & 1);
     int32_t b[DC];
 #pragma unroll
     for (int k = 0; k < DC; ++k) b[k] = nbs[nbi[k] + 9 * xcell];
@@ -653,7 +746,7 @@ __global__ __launch_bounds__(NW_ * 64, 8 / NW_) void k_conv_bfw(const int32_t* _
     for (int k = 0; k < DC; ++k) {
       const int i = wave + NW * k;
       const uint32_t off =
-          b[k] < 0 ? 0x80000000u : (uint32_t)b[k] * (uint32_t)(2 * kk) + ((eb[k] ^ xo) + cb);
+          b[k] < 0 ? 0x80000000u : (uint32_t)b[k] * (uint32_t)(2 * rs) + ((eb[k] ^ xo) + cb);
       lds_bload16(xr, off, lds_addr(i < NDMA ? buf + i * 64 : trash));
     }
   };
@@ -731,6 +824,9 @@ __global__ __launch_bounds__(NW_ * 64, 8 / NW_) void k_conv_bfw(const int32_t* _
   };
 
   v4u W[RW][4];
+  const int nch = SP ? 6 * kk / (32 * HC) : 1;
+  for (int ch = 0; ch < nch; ++ch, ob += 4 * HC) {
+  if (SP && ch > 0) lds_barrier();  // the last chunk's slabs are no longer read
 #pragma unroll
   for (int sl = 0; sl < B::NPRE; ++sl) stage(sl);
 #pragma unroll
@@ -757,6 +853,7 @@ __global__ __launch_bounds__(NW_ * 64, 8 / NW_) void k_conv_bfw(const int32_t* _
     }
   });
   vm_wait0();
+  }
 
   // add the waves' tiles through one 128 x 64 sum in LDS: in round r wave w
   // adds its set r, row block (w + r) % 8, so the eight waves work on eight
@@ -788,6 +885,7 @@ __global__ __launch_bounds__(NW_ * 64, 8 / NW_) void k_conv_bfw(const int32_t* _
     if (row < nrows && n < nn) {
       v4f* dst = reinterpret_cast<v4f*>(out + row * nn + n);
       if (acc_in) sum = *dst + sum;
+      if (SP && oc::s3_bad(sum)) *bad = 1;
       if (relu) {
 #pragma unroll
         for (int j = 0; j < 4; ++j) sum[j] = fmaxf(sum[j], 0.f);
@@ -824,7 +922,10 @@ __global__ __launch_bounds__(NW_ * 64, 8 / NW_) void k_conv_bfw(const int32_t* _
 // group, at the same positions) onto the other four slots of each 256-byte
 // bank row, so 32 lanes read 256 distinct bytes.
 // dyg [ngroups][cout][8] bf16; part [nranges][K^3][cin][cout].
-template <int K, int MAXC, int NW, int GS>
+// SP: fp32 operands in three bf16 parts (x [8 ngroups][3 cin], dyg
+// [3][ngroups][cout][8]); a range is walked once for each of the six products,
+// the sums staying in registers.
+template <int K, int MAXC, int NW, int GS, bool SP>
 __global__ __launch_bounds__(NW * 64, 8 / NW) void k_conv_bf_dw(const int32_t* __restrict__ nbr,
                                                       int64_t ngroups,
                                                       const uint16_t* __restrict__ x, int cin,
@@ -873,6 +974,16 @@ __global__ __launch_bounds__(NW * 64, 8 / NW) void k_conv_bf_dw(const int32_t* _
   const int ncombo = ntap * CB;
   const int64_t gbeg = ngroups * range / nr, gend = ngroups * (range + 1) / nr;
   const int nsteps = (int)((gend - gbeg + GS - 1) / GS);
+  const int rs = SP ? 3 * cin : cin;     // row length of x
+  const int total = SP ? 6 * nsteps : nsteps;
+  // step st is step .s of product .p; past the last product .s runs on past
+  // the range
+  struct At {
+    int p, s;
+  };
+  auto next = [&](At& a) {
+    if (++a.s == nsteps && SP && a.p < 5) a.s = 0, ++a.p;
+  };
 
   // Stage st: the unit's x positions, MAXPOS per group (NXI DMA
   // instructions of 64 pieces; positions past npos read zeros), then the
@@ -888,8 +999,8 @@ __global__ __launch_bounds__(NW * 64, 8 / NW) void k_conv_bf_dw(const int32_t* _
   // instructions) and tb = the byte offset of (group, column) in the step's
   // groups.  Loads go through buffer resources over x and dY, absent rows to
   // an offset past the end (zeros).
-  const sv4 xr = buf_rsrc(x, (uint32_t)(8 * ngroups * cin * 2));
-  const sv4 dr = buf_rsrc(dyg, (uint32_t)(8 * ngroups * cout * 2));
+  const sv4 xr = buf_rsrc(x, (uint32_t)(8 * ngroups * rs * 2));
+  const sv4 dr = buf_rsrc(dyg, (uint32_t)((SP ? 24 : 8) * ngroups * cout * 2));
   int ta[DC];
   uint32_t tb[DC], dk[DC];  // dk: the instruction's byte offset in a stage buffer
 #pragma unroll
@@ -907,7 +1018,7 @@ __global__ __launch_bounds__(NW * 64, 8 / NW) void k_conv_bf_dw(const int32_t* _
       const int ch = c0 + 8 * o;
       ta[k] = p < npos ? 27 * g + ((ux >> 1) + 1) * 9 + ((uy >> 1) + 1) * 3 + ((uz >> 1) + 1) : 0;
       tb[k] = p < npos && ch < cin
-                  ? 2u * (uint32_t)((4 * (ux & 1) + 2 * (uy & 1) + (uz & 1)) * cin + ch)
+                  ? 2u * (uint32_t)((4 * (ux & 1) + 2 * (uy & 1) + (uz & 1)) * rs + ch)
                   : 0x80000000u;
     } else if (i < NXI + NYI) {
       const int gq = i - NXI, co = n0 + lane;
@@ -923,11 +1034,15 @@ __global__ __launch_bounds__(NW * 64, 8 / NW) void k_conv_bf_dw(const int32_t* _
   // slot st % NSLOT (read in one batch, one LDS round trip); formed while the
   // matrix work of an earlier step runs and kept in registers until
   // stage_issue.
+  At as{0, 0}, an{0, 0};  // the next step of stage_src and of nb_dma
   auto stage_src = [&](int st, uint32_t (&src)[DC]) {
-    const int64_t gs = gbeg + GS * (int64_t)st;
+    const int64_t gs = gbeg + GS * (int64_t)as.s;
     const int64_t lf = gend - gs;  // groups of the step inside the range
     const int left = lf < 0 ? 0 : lf > GS ? GS : (int)lf;
-    const uint32_t db = (uint32_t)(8 * gs * cout * 2);
+    const uint32_t db =
+        (uint32_t)(8 * (gs + (SP ? w_part(as.p) * ngroups : 0)) * cout * 2);
+    const uint32_t xa = SP ? 2u * (uint32_t)(x_part(as.p) * cin) : 0u;
+    next(as);
     const int32_t* nb = nbs[st % NSLOT];
     int32_t e[DC];
     static_for<DC>([&](auto kc) {
@@ -936,7 +1051,7 @@ __global__ __launch_bounds__(NW * 64, 8 / NW) void k_conv_bf_dw(const int32_t* _
     });
     static_for<DC>([&](auto kc) {
       constexpr int k = decltype(kc)::value;
-      auto ox = [&] { return e[k] >= 0 ? (uint32_t)e[k] * (uint32_t)(2 * cin) + tb[k] : 0x80000000u; };
+      auto ox = [&] { return e[k] >= 0 ? (uint32_t)e[k] * (uint32_t)(2 * rs) + tb[k] + xa : 0x80000000u; };
       auto od = [&] { return ta[k] < left ? db + tb[k] : 0x80000000u; };
       if constexpr (XK(kc))
         src[k] = ox();
@@ -961,7 +1076,8 @@ __global__ __launch_bounds__(NW * 64, 8 / NW) void k_conv_bf_dw(const int32_t* _
   const uint32_t NB0 = lds_addr(&nbs[0][0]);
   const int ne = wave * 64 + lane, neg = ne / 27;  // entry of the slot, its group
   auto nb_dma = [&](int st) {
-    const int64_t gs = gbeg + GS * (int64_t)st;
+    const int64_t gs = gbeg + GS * (int64_t)an.s;
+    next(an);
     const bool ok = ne < GS * 27 && gs + neg < gend;
     const void* src = ok ? (const void*)(nbr + 27 * gs + ne) : (const void*)&g_minus1;
     lds_load4(src, NB0 + (uint32_t)(((st % NSLOT) * NBP + wave * 64) * 4));
@@ -1059,7 +1175,7 @@ __global__ __launch_bounds__(NW * 64, 8 / NW) void k_conv_bf_dw(const int32_t* _
   // a multiple of st % 3, which the compiler would turn into per-address
   // corrections)
   uint32_t bo = 0, bo2 = 2 * BB;
-  for (int st = 0; st < nsteps; ++st) {
+  for (int st = 0; st < total; ++st) {
     vm_wait_n<DC>();  // stage st and the neighbour rows of step st+3 have landed
     lds_barrier();    // ... everywhere; step st-1 is no longer read
     nb_dma(st + 4);
@@ -1134,13 +1250,21 @@ template <int K, int HC, bool FLIP>
 void launch_chunk(const oc_octree* t, int l, const uint16_t* x, int kk, const uint16_t* wp, int nn,
                   int chunk, float* out, int acc_in, int relu, bool main, hipStream_t s) {
   const int64_t G = t->M[l - 1];
-  const bool wide = wide_tiles(K, kk, nn, 8 * G);
-  const dim3 grid(blocks(G, wide ? BFW_GT : 8), blocks(nn, 64));
-  const dim3 block(wide ? BFW_NW * 64 : 512);
-  auto kern = k_conv_bf<K, HC, FLIP>;
   if constexpr (K == 5) {
-    if (wide) kern = k_conv_bfw<K, HC, FLIP, BFW_GT, BFW_NW>;
+    if (wide_tiles(K, kk, nn, 8 * G)) {
+      const auto kern = k_conv_bfw<K, HC, FLIP, BFW_GT, BFW_NW, false>;
+      const dim3 grid(blocks(G, BFW_GT), blocks(nn, 64)), block(BFW_NW * 64);
+      if (main)
+        oc::launch_main(kern, grid, block, s, (const int32_t*)t->nbr[l], G, x, kk, wp, nn, chunk,
+                        out, acc_in, relu, (uint32_t*)nullptr);
+      else
+        oc::launch(kern, grid, block, 0, s, (const int32_t*)t->nbr[l], G, x, kk, wp, nn, chunk,
+                   out, acc_in, relu, (uint32_t*)nullptr);
+      return;
+    }
   }
+  const auto kern = k_conv_bf<K, HC, FLIP>;
+  const dim3 grid(blocks(G, 8), blocks(nn, 64)), block(512);
   if (main)
     oc::launch_main(kern, grid, block, s, (const int32_t*)t->nbr[l], G, x, kk, wp, nn, chunk, out,
                     acc_in, relu);
@@ -1184,9 +1308,9 @@ void conv_bf16_kernel_name(int K, int cin, int cout, int pass, int64_t rows, cha
                            size_t n) {
   const int kk = pass == 1 ? cout : cin;  // reduction channels of the first chunk
   if (pass == 2)
-    snprintf(buf, n, K == 5 ? "k_conv_bf_dw<5, 10, 4, 4>" : "k_conv_bf_dw<3, 5, 8, 8>");
+    snprintf(buf, n, K == 5 ? "k_conv_bf_dw<5, 10, 4, 4, false>" : "k_conv_bf_dw<3, 5, 8, 8, false>");
   else if (wide_tiles(K, kk, pass == 1 ? cin : cout, rows))
-    snprintf(buf, n, "k_conv_bfw<%d, %d, %s, %d, %d>", K, kk > 32 ? 2 : 1,
+    snprintf(buf, n, "k_conv_bfw<%d, %d, %s, %d, %d, false>", K, kk > 32 ? 2 : 1,
              pass == 1 ? "true" : "false", BFW_GT, BFW_NW);
   else
     snprintf(buf, n, "k_conv_bf<%d, %d, %s>", K, kk > 32 ? 2 : 1, pass == 1 ? "true" : "false");
@@ -1236,15 +1360,96 @@ void conv_bf16_bwd(const oc_octree* t, int l, int K, const uint16_t* x, int cin,
     const int nr = dw_ranges(t, l, K, cin, cout);
     const dim3 grid((unsigned)dw_items(K, nr), blocks(cout, 64), blocks(cin, 64));
     if (K == 5)
-      launch_main(k_conv_bf_dw<5, 10, 4, 4>, grid, dim3(256), s, (const int32_t*)t->nbr[l], G, x,
+      launch_main((k_conv_bf_dw<5, 10, 4, 4, false>), grid, dim3(256), s, (const int32_t*)t->nbr[l], G, x,
                   cin, dyg, cout, nr, part);
     else
-      launch_main(k_conv_bf_dw<3, 5, 8, 8>, grid, dim3(512), s, (const int32_t*)t->nbr[l], G, x,
+      launch_main((k_conv_bf_dw<3, 5, 8, 8, false>), grid, dim3(512), s, (const int32_t*)t->nbr[l], G, x,
                   cin, dyg, cout, nr, part);
     const int64_t E = (int64_t)K3 * cin * cout;
-    oc::launch(k_bf_sum, dim3(blocks(E, 4 * TB)), dim3(TB), 0, s, part, nr, E, dw);
+    oc::launch(k_bf_sum, dim3(blocks(E, 4 * TB)), dim3(TB), 0, s, part, nr, E, dw,
+               (const uint32_t*)nullptr, (uint32_t*)nullptr);
   }
 }
+
+// The three-part path addresses its copies through 32-bit byte offsets.
+static bool sp5_fits(const oc_octree* t, int l, int c) {
+  return t->N[l] * c * 6 < ((int64_t)1 << 31);
+}
+
+bool sp5_fwd_ok(const oc_octree* t, int l, int K, int kk, int nn) {
+  // A tile of 8 groups and 64 columns is one workgroup's serial work over the
+  // whole reduction; below a tile per CU the fp32 kernel's split reduction
+  // fills the chip better.
+  return K == 5 && kk % 32 == 0 && nn % 64 == 0 && sp5_fits(t, l, kk) &&
+         cdiv(t->M[l - 1], BFW_GT) * (nn / 64) >= cu_count();
+}
+
+size_t sp5_fwd_ws(const oc_octree* t, int l, int kk, int nn) {
+  return 256 + align256((size_t)t->N[l] * kk * 6) + align256((size_t)125 * kk * nn * 12);
+}
+
+static void sp_rows(const float* x, int64_t n, int C, uint16_t* x3, hipStream_t s) {
+  oc::launch(k_sp_rows, dim3(blocks(n * C / 8, TB)), dim3(TB), 0, s, x, n * C / 8, C / 8,
+             (int)((uintptr_t)x % 16 == 0), x3);
+}
+
+uint32_t* sp5_fwd(const oc_octree* t, int l, bool flip, const float* x, int kk, const float* w,
+                  int nn, float* out, int relu, void* ws, hipStream_t s) {
+  const int64_t G = t->M[l - 1];
+  uint32_t* flag = (uint32_t*)ws;
+  uint16_t* x3 = (uint16_t*)((char*)ws + 256);
+  uint16_t* wp = (uint16_t*)((char*)x3 + align256((size_t)t->N[l] * kk * 6));
+  oc::launch(k_sp_wprep, dim3(blocks((int64_t)kk / 8 * 125 * nn, TB)), dim3(TB), 0, s, w, 125, kk,
+             nn, (int)flip, wp, flag);
+  sp_rows(x, t->N[l], kk, x3, s);
+  const dim3 grid(blocks(G, BFW_GT), blocks(nn, 64)), block(BFW_NW * 64);
+  const auto kern = flip ? k_conv_bfw<5, 2, true, BFW_GT, BFW_NW, true>
+                         : k_conv_bfw<5, 2, false, BFW_GT, BFW_NW, true>;
+  oc::launch_main(kern, grid, block, s, (const int32_t*)t->nbr[l], G, (const uint16_t*)x3, kk,
+                  (const uint16_t*)wp, nn, 0, out, 0, relu, flag);
+  return flag;
+}
+
+void sp5_fwd_name(bool flip, char* buf, size_t n) {
+  snprintf(buf, n, "k_conv_bfw<5, 2, %s, %d, %d, true>", flip ? "true" : "false", BFW_GT, BFW_NW);
+}
+
+bool sp5_dw_ok(const oc_octree* t, int l, int K, int cin, int cout) {
+  // 64 x 64 channel blocks without padding, and as many groups as the forward
+  return K == 5 && cin % 64 == 0 && cout % 64 == 0 && sp5_fits(t, l, std::max(cin, cout)) &&
+         cdiv(t->M[l - 1], 8) >= cu_count();
+}
+
+size_t sp5_dw_ws(const oc_octree* t, int l, int cin, int cout) {
+  return 256 + align256((size_t)t->N[l] * cin * 6) + align256((size_t)t->N[l] * cout * 6) +
+         (size_t)dw_ranges(t, l, 5, cin, cout) * 125 * cin * cout * sizeof(float);
+}
+
+uint32_t* sp5_dw(const oc_octree* t, int l, const float* x, int cin, const float* dy, int cout,
+                 float* dw, void* ws, hipStream_t s) {
+  const int64_t G = t->M[l - 1], N = t->N[l], E = (int64_t)125 * cin * cout;
+  uint32_t* flag = (uint32_t*)ws;
+  uint16_t* x3 = (uint16_t*)((char*)ws + 256);
+  uint16_t* dyg = (uint16_t*)((char*)x3 + align256((size_t)N * cin * 6));
+  float* part = (float*)((char*)dyg + align256((size_t)N * cout * 6));
+  sp_rows(x, N, cin, x3, s);
+  oc::launch(k_sp_cvt_g, dim3(blocks(G * cout, TB)), dim3(TB), 0, s, dy, G, cout, dyg, flag);
+  const int nr = dw_ranges(t, l, 5, cin, cout);
+  const dim3 grid((unsigned)dw_items(5, nr), blocks(cout, 64), blocks(cin, 64));
+  launch_main((k_conv_bf_dw<5, 10, 4, 4, true>), grid, dim3(256), s, (const int32_t*)t->nbr[l], G,
+              (const uint16_t*)x3, cin, (const uint16_t*)dyg, cout, nr, part);
+  oc::launch(k_bf_sum, dim3(blocks(E, 4 * TB)), dim3(TB), 0, s, (const float*)part, nr, E, dw,
+             (const uint32_t*)nullptr, flag);
+  return flag;
+}
+
+void sp5_sum_gated(const float* part, int nparts, int64_t n, float* out, const uint32_t* gate,
+                   hipStream_t s) {
+  oc::launch(k_bf_sum, dim3(blocks(n, 4 * TB)), dim3(TB), 0, s, part, nparts, n, out, gate,
+             (uint32_t*)nullptr);
+}
+
+void sp5_dw_name(char* buf, size_t n) { snprintf(buf, n, "k_conv_bf_dw<5, 10, 4, 4, true>"); }
 
 void round_bf16(const float* x, int64_t n, uint16_t* y, hipStream_t s) {
   const bool vec = ((uintptr_t)x % 16 == 0) && ((uintptr_t)y % 16 == 0);

@@ -54,8 +54,12 @@ void conv_s1_bwd_data_pool_f32(const oc_octree* t, int l, int K, const float* dy
 // Number of [K^3][cin][cout] fp32 partial sums conv_s1_bwd_weight_f32 needs.
 size_t conv_s1_dw_parts(const oc_octree* t, int l, int K, int cin, int cout);
 
-// dw [K^3][cin][cout] = weight gradient of a stride-1 convolution; part holds
-// conv_s1_dw_parts() partial sums.  defer: leave the partial sums in part
+// Bytes of workspace conv_s1_bwd_weight_f32 needs: the partial sums, or what
+// the kernel on three bf16 parts takes.
+size_t conv_s1_dw_ws(const oc_octree* t, int l, int K, int cin, int cout);
+
+// dw [K^3][cin][cout] = weight gradient of a stride-1 convolution; part:
+// conv_s1_dw_ws() bytes.  defer: leave the partial sums in part
 // (dw not written), for a later sum_partials_multi.
 void conv_s1_bwd_weight_f32(const oc_octree* t, int l, int K, const float* x, int cin,
                             const float* dy, int cout, float* dw, float* part, hipStream_t s,

@@ -31,6 +31,7 @@
 #include "conv_mfma.h"
 #include "pool_fuse.h"
 
+#include "conv_bf16.h"
 #include "conv_cin.h"
 #include "conv_split.h"
 
@@ -121,12 +122,15 @@ __device__ __forceinline__ int32_t tile_src(const int32_t* __restrict__ nb, int 
 // reduction channels, cps chunks each.  With one split the result (ReLU
 // applied if relu) goes to out; otherwise split z writes its partial sum to
 // part[z][row][n] and k_sum_split finishes.
+// gate != NULL: the launch does its work only when *gate is set.
 template <int K, int V, int MR, int NR, int WM, bool FLIP, bool VEC>
 __global__ __launch_bounds__(TB) void k_conv_tile(const int32_t* __restrict__ nbr, int64_t ngroups,
                                                   const float* __restrict__ x, int kk,
                                                   const float* __restrict__ w, int nn,
                                                   float* __restrict__ out, int relu, int cps,
-                                                  float* __restrict__ part) {
+                                                  float* __restrict__ part,
+                                                  const uint32_t* __restrict__ gate) {
+  if (gate && *gate == 0) return;
   constexpr int WN = WAVES / WM;
   constexpr int R = (K - 1) / 2, S = K + 1, K2 = K * K, K3 = K2 * K, S3 = S * S * S;
   constexpr int PX = S * S + 2;  // tile rows per x-slab (two padding rows)
@@ -691,7 +695,9 @@ template <int K, int VA, int VB, int TT, int MB, int WT>
 __global__ __launch_bounds__(TB) void k_conv_dw(const int32_t* __restrict__ nbr, int64_t ngroups,
                                                 int64_t gchunk, const float* __restrict__ x,
                                                 int cin, const float* __restrict__ dy, int cout,
-                                                float* __restrict__ part) {
+                                                float* __restrict__ part,
+                                                const uint32_t* __restrict__ gate) {
+  if (gate && *gate == 0) return;
   constexpr int R = (K - 1) / 2, K3 = K * K * K;
   constexpr bool FLAT = MB > 0;
   constexpr int NA = FLAT ? MB : TT;  // A operands per reduction step
@@ -1278,7 +1284,7 @@ TileCfg pick_tile(int K, int64_t G, int kk, int nn) {
 template <int K, int V, int MR, int NR, int WM, bool FLIP, bool VEC>
 void launch_tile(const oc_octree* t, int l, const TileCfg& c, const float* x, int kk,
                  const float* w, int nn, float* out, int relu, float* part, hipStream_t s,
-                 const RouteOut* ro = nullptr) {
+                 const RouteOut* ro, const uint32_t* gate) {
   const auto kernel = k_conv_tile<K, V, MR, NR, WM, FLIP, VEC>;
   static const int occ = [&] {
     int n = 0;
@@ -1294,8 +1300,12 @@ void launch_tile(const oc_octree* t, int l, const TileCfg& c, const float* x, in
   int64_t px = std::min<int64_t>(ntile, std::max<int64_t>(1, (int64_t)oc::cu_count() * occ / gyz));
   if (px >= 8) px -= px % 8;
   dim3 grid((unsigned)px, (unsigned)oc::cdiv(nn, BN), (unsigned)c.splits);
-  oc::launch_main(kernel, grid, dim3(TB), s, (const int32_t*)t->nbr[l], G, x, kk, w, nn, out, relu,
-                  c.cps, part);
+  if (gate)
+    oc::launch(kernel, grid, dim3(TB), 0, s, (const int32_t*)t->nbr[l], G, x, kk, w, nn, out, relu,
+               c.cps, part, gate);
+  else
+    oc::launch_main(kernel, grid, dim3(TB), s, (const int32_t*)t->nbr[l], G, x, kk, w, nn, out,
+                    relu, c.cps, part, gate);
   if (ro) {  // input gradient routed on (relu is 0)
     route_parts(t, l, c.splits > 1 ? part : out, c.splits, nn, *ro, s);
   } else if (c.splits > 1) {
@@ -1307,7 +1317,14 @@ template <bool FLIP>
 void dispatch_tile(const oc_octree* t, int l, int K, const float* x, int kk, const float* w,
                    int nn, float* out, int relu, float* part, hipStream_t s,
                    const RouteOut* ro = nullptr) {
-  const TileCfg c = pick_tile(K, t->M[l - 1], kk, nn);
+  TileCfg c = pick_tile(K, t->M[l - 1], kk, nn);
+  const uint32_t* gate = nullptr;
+  if (oc::sp5_fwd_ok(t, l, K, kk, nn) && (uintptr_t)out % 16 == 0) {
+    // the launch below then works out again, in one split, what is not finite
+    gate = oc::sp5_fwd(t, l, FLIP, x, kk, w, nn, out, relu, part, s);
+    c.splits = 1;
+    c.cps = (int)oc::cdiv(kk, 4 * c.V);
+  }
   if (c.v2) {
     const oc::Sp3Cfg sc = oc::sp3_pick(t->M[l - 1], kk, nn);
     oc::sp3_launch(t, l, sc, FLIP, x, kk, w, nn, out, relu, part, nullptr, s);
@@ -1319,7 +1336,7 @@ void dispatch_tile(const oc_octree* t, int l, int K, const float* x, int kk, con
   }
 #define OC_TILE(K_, V_, MR_, NR_, WM_, VEC_)                                                    \
   if (K == K_ && c.V == V_ && c.MR == MR_ && c.NR == NR_ && c.WM == WM_ && c.VEC == VEC_) {     \
-    launch_tile<K_, V_, MR_, NR_, WM_, FLIP, VEC_>(t, l, c, x, kk, w, nn, out, relu, part, s, ro); \
+    launch_tile<K_, V_, MR_, NR_, WM_, FLIP, VEC_>(t, l, c, x, kk, w, nn, out, relu, part, s, ro, gate); \
     return;                                                                                     \
   }
   OC_TILE(3, 1, 2, 1, 4, true) OC_TILE(3, 1, 2, 1, 4, false)
@@ -1462,16 +1479,15 @@ DwCfg pick_dw(int K, int64_t G, int cin, int cout) {
 
 template <int K, int VA, int VB, int TT, int MB>
 void launch_dw(const oc_octree* t, int l, const DwCfg& c, const float* x, int cin,
-               const float* dy, int cout, float* part, hipStream_t s) {
-  if (c.WT == 4) {
-    dim3 grid((unsigned)c.nchunks, (unsigned)oc::cdiv(c.tiles, 4));
-    oc::launch_main(k_conv_dw<K, VA, VB, TT, MB, 4>, grid, dim3(TB), s,
-                    (const int32_t*)t->nbr[l], t->M[l - 1], c.gchunk, x, cin, dy, cout, part);
-    return;
-  }
-  dim3 grid((unsigned)c.nchunks, (unsigned)c.tiles);
-  oc::launch_main(k_conv_dw<K, VA, VB, TT, MB, 1>, grid, dim3(TB), s,
-                     (const int32_t*)t->nbr[l], t->M[l - 1], c.gchunk, x, cin, dy, cout, part);
+               const float* dy, int cout, float* part, const uint32_t* gate, hipStream_t s) {
+  const auto kernel = c.WT == 4 ? k_conv_dw<K, VA, VB, TT, MB, 4> : k_conv_dw<K, VA, VB, TT, MB, 1>;
+  const dim3 grid((unsigned)c.nchunks, (unsigned)(c.WT == 4 ? oc::cdiv(c.tiles, 4) : c.tiles));
+  if (gate)
+    oc::launch(kernel, grid, dim3(TB), 0, s, (const int32_t*)t->nbr[l], t->M[l - 1], c.gchunk, x,
+               cin, dy, cout, part, gate);
+  else
+    oc::launch_main(kernel, grid, dim3(TB), s, (const int32_t*)t->nbr[l], t->M[l - 1], c.gchunk, x,
+                    cin, dy, cout, part, gate);
 }
 
 // Forward of a 3- or 4-channel input (the first layer): k_conv_cin.
@@ -1498,6 +1514,10 @@ void conv_s1_kernel_name(const oc_octree* t, int l, int K, int cin, int cout, in
                d.NBN, d.GS, d.xv ? "true" : "false", d.HV);
       return;
     }
+    if (sp5_dw_ok(t, l, K, cin, cout)) {
+      sp5_dw_name(buf, n);
+      return;
+    }
     const DwCfg c = pick_dw(K, t->M[l - 1], cin, cout);
     snprintf(buf, n, "k_conv_dw<%d, %d, %d, %d, %d, %d>", K, c.VA, c.VB, c.TT, c.MB, c.WT);
     return;
@@ -1512,13 +1532,18 @@ void conv_s1_kernel_name(const oc_octree* t, int l, int K, int cin, int cout, in
     oc::sp3_name(oc::sp3_pick(t->M[l - 1], kk, nn), pass == 1, pooled, buf, n);
     return;
   }
+  if (sp5_fwd_ok(t, l, K, kk, nn)) {
+    sp5_fwd_name(pass == 1, buf, n);
+    return;
+  }
   snprintf(buf, n, "k_conv_tile<%d, %d, %d, %d, %d, %s, %s>", K, c.V, c.MR, c.NR, c.WM,
            pass == 0 ? "false" : "true", c.VEC ? "true" : "false");
 }
 
 size_t conv_s1_tile_ws(const oc_octree* t, int l, int K, int kk, int nn) {
   const TileCfg c = pick_tile(K, t->M[l - 1], kk, nn);
-  return c.splits > 1 ? (size_t)c.splits * t->N[l] * nn * sizeof(float) : 0;
+  const size_t split = c.splits > 1 ? (size_t)c.splits * t->N[l] * nn * sizeof(float) : 0;
+  return oc::sp5_fwd_ok(t, l, K, kk, nn) ? std::max(split, oc::sp5_fwd_ws(t, l, kk, nn)) : split;
 }
 
 void conv_s1_fwd_f32(const oc_octree* t, int l, int K, const float* x, int cin, const float* w,
@@ -1591,6 +1616,12 @@ size_t conv_s1_dw_parts(const oc_octree* t, int l, int K, int cin, int cout) {
   return (size_t)np;
 }
 
+size_t conv_s1_dw_ws(const oc_octree* t, int l, int K, int cin, int cout) {
+  const size_t parts = conv_s1_dw_parts(t, l, K, cin, cout) * K * K * K * cin * cout * sizeof(float);
+  if (!sp5_dw_ok(t, l, K, cin, cout)) return parts;
+  return std::max(256 + parts, sp5_dw_ws(t, l, cin, cout));  // 256: the flag
+}
+
 void conv_s1_bwd_weight_f32(const oc_octree* t, int l, int K, const float* x, int cin,
                             const float* dy, int cout, float* dw, float* part,
                             hipStream_t s, bool defer) {
@@ -1609,9 +1640,16 @@ void conv_s1_bwd_weight_f32(const oc_octree* t, int l, int K, const float* x, in
     return;
   }
   const DwCfg c = pick_dw(K, t->M[l - 1], cin, cout);
+  // (deferred sums are the fp32 kernel's: oc_conv_dw_partials names their number)
+  const uint32_t* gate = nullptr;
+  if (!defer && oc::sp5_dw_ok(t, l, K, cin, cout) && (uintptr_t)dw % 16 == 0) {
+    // the launch below then works out again what is not finite
+    gate = oc::sp5_dw(t, l, x, cin, dy, cout, dw, part, s);
+    part += 64;  // behind the flag
+  }
 #define OC_DW(K_, VA_, VB_, TT_, MB_)                                                       \
   if (K == K_ && c.VA == VA_ && c.VB == VB_ && c.TT == TT_ && c.MB == MB_) {               \
-    launch_dw<K_, VA_, VB_, TT_, MB_>(t, l, c, x, cin, dy, cout, part, s);                 \
+    launch_dw<K_, VA_, VB_, TT_, MB_>(t, l, c, x, cin, dy, cout, part, gate, s);           \
   } else
   // PERM mode, K = 3
   OC_DW(3, 4, 4, 1, 0) OC_DW(3, 4, 2, 1, 0) OC_DW(3, 2, 4, 1, 0) OC_DW(3, 4, 1, 3, 0)
@@ -1631,7 +1669,10 @@ void conv_s1_bwd_weight_f32(const oc_octree* t, int l, int K, const float* x, in
     oc::set_error("no weight-gradient kernel for K=%d cin=%d cout=%d", K, cin, cout);
   }
 #undef OC_DW
-  if (!defer) sum_parts(part, (int)c.nchunks, entries, dw, s);
+  if (gate)
+    oc::sp5_sum_gated(part, (int)c.nchunks, entries, dw, gate, s);
+  else if (!defer)
+    sum_parts(part, (int)c.nchunks, entries, dw, s);
 }
 
 void sum_partials(const float* part, int np, int64_t n, float* out, hipStream_t s) {

@@ -6,6 +6,8 @@ row and weight-gradient entry, except the 5x5x5 64->64 layer of wide_d7,
 whose every row and entry is checked through random channel projections
 (each implied by the elementwise rule) beside exact contiguous tiles and
 exact entries of every (tap, 16 x 16 channel) block of dW."""
+import math
+
 import numpy as np
 import pytest
 import torch
@@ -189,6 +191,73 @@ def test_conv_split_4gib():
     y = oc.oc_conv_fwd(tree, 8, 3, 1, x, w)
     ys = oc.oc_conv_fwd(tree, 8, 3, 1, x[:, -16:].contiguous(), w[:, -16:].contiguous())
     assert torch.equal(y, ys)
+
+
+SPLIT_K5 = [  # seed, B, n, depth, cin, cout, which passes run on three bf16 parts
+    (301, 7, 6000, 6, 64, 64, (1, 1, 1)),    # one block of channels and columns
+    (302, 7, 6003, 6, 32, 64, (1, 0, 0)),    # three chunks of two products each
+    (303, 1, 900, 5, 512, 96, (0, 1, 0)),    # 1.5 chunks a product, eight column blocks
+    (304, 7, 6000, 6, 64, 128, (1, 1, 1)),   # two column blocks
+]
+
+
+@pytest.mark.parametrize("seed,B,n,depth,cin,cout,on", SPLIT_K5)
+def test_conv_k5_split_parts(seed, B, n, depth, cin, cout, on):
+    """K = 5 fp32 layers on the bf16 kernels in three parts, against 64-bit
+    sums: below 1e-6 of the result's norm in each pass, as for K = 3 (one bf16
+    part would give 2e-3); then what is not finite, in each pass."""
+    oc = _oc()
+    print(f"[split5] seed={seed} B={B} d={depth} {cin}->{cout}", flush=True)
+    ref, tree = _trees(*synth.random_cloud(seed, B, n, "union"), depth)
+    names = [oc.oc_conv_kernel(tree, depth, 5, 1, cin, cout, p) for p in range(3)]
+    assert tuple(int(s.startswith("k_conv_bf") and s.endswith("true>")) for s in names) == on, names
+    rng = np.random.default_rng(seed)
+    N = ref.num(depth)
+    x = rng.standard_normal((N, cin)).astype(np.float32)
+    w = (rng.standard_normal((125, cin, cout)) / np.sqrt(125 * cin)).astype(np.float32)
+    dy = rng.standard_normal((N, cout)).astype(np.float32)
+    nb = torch.as_tensor(np.asarray(ref.neighbors(depth, 5))).long()
+    nb = torch.where(nb < 0, N, nb).cuda()
+
+    def pad(v):
+        return torch.cat([_cuda(v), torch.zeros((1, v.shape[1]), device="cuda")]).double()
+
+    def want(x, w, dy):
+        xp, dp, w64 = pad(x), pad(dy), _cuda(w).double()
+        y = torch.zeros((N, cout), device="cuda", dtype=torch.float64)
+        dx = torch.zeros((N, cin), device="cuda", dtype=torch.float64)
+        dw = torch.empty((125, cin, cout), device="cuda", dtype=torch.float64)
+        for k in range(125):
+            c = xp[nb[:, k]]
+            y += c @ w64[k]
+            dx += dp[nb[:, 124 - k]] @ w64[k].t().contiguous()
+            dw[k] = c.t().contiguous() @ dp[:N]
+        return y, dx, dw
+
+    def got(x, w, dy):
+        y = oc.oc_conv_fwd(tree, depth, 5, 1, _cuda(x), _cuda(w))
+        return (y,) + tuple(oc.oc_conv_bwd(tree, depth, 5, 1, _cuda(x), _cuda(w), _cuda(dy)))
+
+    # (a pass that stays on the fp32 kernel: the bound of M roundings, as below)
+    for tag, g, r, sp, M in zip(("y", "dx", "dw"), got(x, w, dy), want(x, w, dy), on,
+                                (125 * cin, 125 * cout, N)):
+        tol = 1e-6 if sp else math.sqrt(M) * 2.0 ** -24
+        assert torch.linalg.norm(g.double() - r) <= tol * torch.linalg.norm(r), tag
+    yr = oc.oc_conv_fwd(tree, depth, 5, 1, _cuda(x), _cuda(w), relu=True)
+    assert torch.equal(yr, got(x, w, dy)[0].clamp(min=0))
+    w[3, 0, :] = 1.0  # exact in bf16: its other parts are zero
+    for i, v in enumerate((np.inf, -np.inf, np.nan, 3.4e38)):
+        x[(7 + 41 * i) % N, i] = v
+    dy[5, 1] = np.inf
+    for tag, g, r in zip(("y", "dx", "dw"), got(x, w, dy), want(x, w, dy)):
+        r = r.float()  # overflows as fp32 does
+        assert torch.equal(g.isfinite(), r.isfinite()) and torch.equal(g.isnan(), r.isnan()), tag
+        ok = r.isfinite() & (r.abs() < 1e30)  # (sums with a term of 3.4e38 left out)
+        # plain fp32 sums of M terms in sequence: M roundings of either sign, each
+        # below half an ulp of the running sum, which stays about the largest result
+        M = N if tag == "dw" else 125 * (cin if tag == "y" else cout)
+        tol = math.sqrt(M) * 2.0 ** -24 * float(r[ok].abs().max())
+        assert float((g[ok] - r[ok]).abs().max()) <= tol, (tag, tol)
 
 
 SR_SMALL = [  # seed, B, n, depth, stride, cin, cout, relu, bf16
