@@ -868,7 +868,7 @@ __global__ __launch_bounds__(TB) void k_conv_dw(const int32_t* __restrict__ nbr,
 }
 
 // ---------------------------------------------------------------------------
-// Weight gradient through LDS, K = 3:
+// Weight gradient through LDS, K = 3, cin < 16:
 //   dW[k][c][n] = sum over octants i of x[nb(i,k)][c] * dY[i][n]
 // A workgroup takes a chunk of sibling groups and, GS groups at a time,
 // stages their (K+1)^3 x CW tiles of x and their 8 GS rows x BN columns of dY
@@ -876,31 +876,22 @@ __global__ __launch_bounds__(TB) void k_conv_dw(const int32_t* __restrict__ nbr,
 // MFMA reduction index is the octant: the children 4h + q (q = lane / 16) of
 // a group, so lane l supplies A[c = l%16][child] from the tile position of
 // that child's tap and B[child][n = l%16] from the dY rows; one staged dY
-// value feeds the MFMAs of every tap.
-// Tiled mode (cin >= 16): the workgroup owns channels 16 cbk.. 16 cbk+15 and
-// columns BN nbk..; wave w takes taps w, w+4, ... (NJ at most).
-// FLAT mode (cin < 16): M runs over (tap, channel) pairs m = tap cin + c,
-// which is the row of dW itself; blocks of 16 pairs are dealt to the waves
-// (rotated by workgroup so that no SIMD always gets the short share).
-// HV = 2 (tiled mode only): the workgroup is two such 4-wave halves that
-// take alternate stages of the chunk, each with its own staging buffers; at
-// the end they add their accumulators through LDS (half 0 keeps the first
-// ceil(NJ/2) blocks, half 1 the rest), so a workgroup holds twice the
-// octants per partial and the partial traffic halves.
-// Workgroup (chunk, tile) writes part[chunk][K3 cin][cout] for its block of
-// dW (every entry of the block, zeros included); a second kernel adds the
-// chunks in a fixed order.  XV: cin is a multiple of 4 (x rows read as
+// value feeds the MFMAs of every tap.  M runs over (tap, channel) pairs m =
+// tap cin + c, which is the row of dW itself; blocks of 16 pairs are dealt to
+// the waves (rotated by workgroup so that no SIMD always gets the short
+// share).  Workgroup (chunk, tile) writes part[chunk][K3 cin][cout] for its
+// block of dW (every entry of the block, zeros included); a second kernel adds
+// the chunks in a fixed order.  XV: cin is a multiple of 4 (x rows read as
 // float4); cout must be a multiple of 4.
-template <bool FLAT, int CW, int NBN, int GS, bool XV, int HV>
-__global__ __launch_bounds__(TB * HV) void k_conv_dwt(const int32_t* __restrict__ nbr,
+template <int CW, int NBN, int GS, bool XV>
+__global__ __launch_bounds__(TB) void k_conv_dwt(const int32_t* __restrict__ nbr,
                                                       int64_t ngroups, int64_t gchunk,
                                                       const float* __restrict__ x, int cin,
                                                       const float* __restrict__ dy, int cout,
                                                       float* __restrict__ part) {
-  static_assert(HV == 1 || (HV == 2 && !FLAT), "two halves in tiled mode only");
   constexpr int R = 1, S = 4, K3 = 27, S3 = 64;
-  // M blocks per wave at most: 27 taps, or ceil(27 cin / 16) <= 7, 14, 27 pairs
-  constexpr int NJ = !FLAT ? 7 : CW == 4 ? 2 : CW == 8 ? 4 : 7;
+  // M blocks per wave at most: ceil(27 cin / 16) <= 7, 14, 27
+  constexpr int NJ = CW == 4 ? 2 : CW == 8 ? 4 : 7;
   constexpr int SY = S + 2, PX = S * SY, P3 = S * PX;  // tile row of (px,py,pz): px PX + py SY + pz
   constexpr int RS = CW, F4 = CW / 4;
   constexpr int BN = 16 * NBN;
@@ -911,47 +902,30 @@ __global__ __launch_bounds__(TB * HV) void k_conv_dwt(const int32_t* __restrict_
   constexpr int NY = (NYE + TB - 1) / TB;
   static_assert(TB % (S3 * F4) == 0 && GS % GPP == 0, "x staging covers the stage");
   static_assert(NX <= 32 && NY <= 32, "validity bits fit a word");
-  constexpr int NA = GS * P3 * RS, NB = 8 * GS * BNS;      // floats of one half's buffers
-  constexpr int NRED = HV == 2 ? NJ * NBN * WAVES * 64 * 4 : 0;  // floats of the reduction
-  constexpr int NSM = HV * (NA + NB) > NRED ? HV * (NA + NB) : NRED;
-  __shared__ __attribute__((aligned(16))) float smem[NSM];
+  constexpr int NA = GS * P3 * RS, NB = 8 * GS * BNS;      // floats of the buffers
+  __shared__ __attribute__((aligned(16))) float At[NA], Bt[NB];
 
-  const int tid = threadIdx.x & (TB - 1), lane = tid & 63;
-  const int half = HV == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 8);
+  const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform: scalar branches
-  float* const At = smem + half * (NA + NB);
-  float* const Bt = At + NA;
   const int li = lane & 15, q = lane >> 4;
-  const int nCB = FLAT ? 1 : (cin + 15) / 16;
-  const int cbk = (int)(blockIdx.y % nCB), nbk = (int)(blockIdx.y / nCB);
-  const int c0 = FLAT ? 0 : 16 * cbk, n0 = BN * nbk;
+  const int n0 = BN * (int)blockIdx.y;
   const int64_t gb = (int64_t)blockIdx.x * gchunk;
   const int64_t ge = gb + gchunk < ngroups ? gb + gchunk : ngroups;
-  // stages of GS groups; half h takes stages h, h + HV, ...
-  const int nsub = gb < ge ? (int)((ge - gb + GS * HV - 1) / (GS * HV)) : 0;
-  const int nmb = FLAT ? (K3 * cin + 15) / 16 : K3;  // M blocks (taps when tiled)
-  const int rot = FLAT ? (int)(blockIdx.x % WAVES) : 0;
+  const int nsub = gb < ge ? (int)((ge - gb + GS - 1) / GS) : 0;  // stages of GS groups
+  const int nmb = (K3 * cin + 15) / 16;                           // M blocks
+  const int rot = (int)(blockIdx.x % WAVES);
   const int mb0 = (wave + rot) % WAVES;
   const int njw = nmb > mb0 ? (nmb - mb0 + WAVES - 1) / WAVES : 0;  // blocks of this wave
 
   // M blocks of this wave: block mb[j] = 4 j + mb0; the lane's LDS offset
-  // (tap position and channel) and, in FLAT mode, validity
+  // (tap position and channel) and validity
   int aoff[NJ];
   bool alive[NJ];
 #pragma unroll
   for (int j = 0; j < NJ; ++j) {
-    const int mb = 4 * j + mb0;
-    int tap, ch;
-    if constexpr (FLAT) {
-      const int m = 16 * mb + li;
-      alive[j] = m < K3 * cin;
-      tap = alive[j] ? m / cin : 0;
-      ch = alive[j] ? m - tap * cin : 0;
-    } else {
-      alive[j] = mb < K3;
-      tap = alive[j] ? mb : 0;
-      ch = li;
-    }
+    const int m = 16 * (4 * j + mb0) + li;
+    alive[j] = m < K3 * cin;
+    const int tap = alive[j] ? m / cin : 0, ch = alive[j] ? m - tap * cin : 0;
     aoff[j] = ((tap / 9) * PX + ((tap / 3) % 3) * SY + tap % 3) * RS + ch;
   }
   // tile row of child 4h + q at tap offset -R on every axis: h PX + (q>>1) SY + (q&1)
@@ -970,7 +944,7 @@ __global__ __launch_bounds__(TB * HV) void k_conv_dwt(const int32_t* __restrict_
   const int a_ux = a_px - R, a_uy = a_py - R, a_uz = a_pz - R;
   const int a_slot = ((a_ux >> 1) + 1) * 9 + ((a_uy >> 1) + 1) * 3 + ((a_uz >> 1) + 1);
   const int a_coff = 4 * (a_ux & 1) + 2 * (a_uy & 1) + (a_uz & 1);
-  const int a_ch = c0 + 4 * a_f;
+  const int a_ch = 4 * a_f;
 
   int32_t nbc[NX], nbn[NX];
   uint32_t okc = 0, okn = 0;
@@ -978,7 +952,7 @@ __global__ __launch_bounds__(TB * HV) void k_conv_dwt(const int32_t* __restrict_
     ok = 0;
 #pragma unroll
     for (int i = 0; i < NX; ++i) {
-      const int64_t g = gb + (int64_t)(HV * s + half) * GS + a_g + GPP * i;
+      const int64_t g = gb + (int64_t)s * GS + a_g + GPP * i;
       const bool live = g < ge;
       v[i] = nbr[live ? 27 * g + a_slot : 0];
       ok |= (uint32_t)live << i;
@@ -1020,7 +994,7 @@ __global__ __launch_bounds__(TB * HV) void k_conv_dwt(const int32_t* __restrict_
     for (int i = 0; i < NY; ++i) {
       const int e = tid + i * TB;
       const int r = e / (BN / 4), gn = n0 + 4 * (e % (BN / 4));
-      const int64_t g0 = gb + (int64_t)(HV * s + half) * GS;
+      const int64_t g0 = gb + (int64_t)s * GS;
       const bool live = e < NYE && g0 + r / 8 < ge && gn < cout;
       const int64_t off = live ? (8 * g0 + r) * cout + gn : 0;
       ry[i] = *reinterpret_cast<const v4f*>(dy + off);
@@ -1084,51 +1058,21 @@ __global__ __launch_bounds__(TB * HV) void k_conv_dwt(const int32_t* __restrict_
     }
   }
 
-  // halves add their accumulators: block j goes to half j < JH ? 0 : 1
-  constexpr int JH = (NJ + 1) / 2;
-  if constexpr (HV == 2) {
-    v4f* red = reinterpret_cast<v4f*>(smem);
-    __syncthreads();  // the last stage's LDS reads are done
-#pragma unroll
-    for (int j = 0; j < NJ; ++j)
-      if ((j < JH) != (half == 0))
-#pragma unroll
-        for (int nb = 0; nb < NBN; ++nb) red[((j * NBN + nb) * WAVES + wave) * 64 + lane] = acc[j][nb];
-    __syncthreads();
-#pragma unroll
-    for (int j = 0; j < NJ; ++j)
-      if ((j < JH) == (half == 0))
-#pragma unroll
-        for (int nb = 0; nb < NBN; ++nb) {
-          const v4f o = red[((j * NBN + nb) * WAVES + wave) * 64 + lane];
-#pragma unroll
-          for (int r = 0; r < 4; ++r) acc[j][nb][r] += o[r];
-        }
-  }
-
   // accumulator r of lane l: M row 4(l/16) + r, column l % 16
   const int64_t entries = (int64_t)K3 * cin * cout;
   float* pp = part + (int64_t)blockIdx.x * entries;
 #pragma unroll
   for (int j = 0; j < NJ; ++j) {
     const int mb = 4 * j + mb0;
-    if (j >= njw || (HV == 2 && (j < JH) != (half == 0))) continue;
+    if (j >= njw) continue;
 #pragma unroll
     for (int nb = 0; nb < NBN; ++nb) {
       const int n = n0 + 16 * nb + li;
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int i = 4 * q + r;
-        int m;
-        bool ok;
-        if constexpr (FLAT) {
-          m = 16 * mb + i;
-          ok = m < K3 * cin;
-        } else {
-          ok = c0 + i < cin;
-          m = mb * cin + c0 + i;
-        }
-        if (ok && n < cout) pp[(int64_t)m * cout + n] = acc[j][nb][r];
+        const int m = 16 * mb + i;
+        if (m < K3 * cin && n < cout) pp[(int64_t)m * cout + n] = acc[j][nb][r];
       }
     }
   }
@@ -1345,11 +1289,11 @@ void dispatch_tile(const oc_octree* t, int l, int K, const float* x, int kk, con
 #undef OC_TILE
 }
 
-// Weight gradient through LDS (k_conv_dwt): K = 3 with cout a multiple of 4,
-// and cin a multiple of 4 when cin >= 16.
+// Weight gradient through LDS: K = 3 with cout a multiple of 4; cin < 16
+// (k_conv_dwt), or a multiple of 4 (k_conv_dws).
 struct DwtCfg {
   bool flat, xv;
-  int CW, NBN, GS, HV, tiles;
+  int CW, NBN, GS, tiles;
   int64_t gchunk, nchunks;
 };
 
@@ -1366,18 +1310,14 @@ bool pick_dwt(int K, int64_t G, int cin, int cout, DwtCfg* c) {
     c->NBN = cout <= 16 ? 1 : 2;
   } else {
     c->CW = 16, c->GS = 4;
-    // 32 output channels per workgroup: 64 writes twice the partial sums (one
-    // per resident workgroup) and 16 stages x twice as often; both were
-    // measured slower on the depth-2..5 layers of the 32-shape batch
-    c->NBN = cout >= 32 ? 2 : 1;
+    c->NBN = cout > 16 ? 2 : 1;
   }
-  c->HV = c->flat ? 1 : 2;
   const int nCB = c->flat ? 1 : (int)oc::cdiv(cin, 16);
   c->tiles = nCB * (int)oc::cdiv(cout, 16 * c->NBN);
   const int64_t entries = (int64_t)27 * cin * cout;
   // one round of resident workgroups (at least one stage of groups each),
-  // partial sums capped at 16M floats
-  const int64_t slots = (int64_t)oc::cu_count() * dwt_occupancy(*c);
+  // partial sums capped at 16M floats; k_conv_dws: one workgroup per CU
+  const int64_t slots = (int64_t)oc::cu_count() * (c->flat ? dwt_occupancy(*c) : 1);
   int64_t chunks = std::max<int64_t>(1, slots / c->tiles);
   chunks = std::min<int64_t>(chunks, std::max<int64_t>(1, (int64_t(16) << 20) / entries));
   c->gchunk = std::max<int64_t>(c->GS, oc::cdiv(std::max<int64_t>(G, 1), chunks));
@@ -1385,20 +1325,20 @@ bool pick_dwt(int K, int64_t G, int cin, int cout, DwtCfg* c) {
   return true;
 }
 
-template <bool FLAT, int CW, int NBN, int GS, bool XV, int HV>
+template <int CW, int NBN, int GS, bool XV>
 void launch_dwt(const oc_octree* t, int l, const DwtCfg& c, const float* x, int cin,
                 const float* dy, int cout, float* part, hipStream_t s) {
   dim3 grid((unsigned)c.nchunks, (unsigned)c.tiles);
-  oc::launch_main(k_conv_dwt<FLAT, CW, NBN, GS, XV, HV>, grid, dim3(TB * HV), s, (const int32_t*)t->nbr[l],
+  oc::launch_main(k_conv_dwt<CW, NBN, GS, XV>, grid, dim3(TB), s, (const int32_t*)t->nbr[l],
                   t->M[l - 1], c.gchunk, x, cin, dy, cout, part);
 }
 
 // Resident workgroups per CU of the configuration's kernel (cached).
-template <bool FLAT, int CW, int NBN, int GS, bool XV, int HV>
+template <int CW, int NBN, int GS, bool XV>
 int dwt_occ() {
   static const int occ = [] {
     int n = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_conv_dwt<FLAT, CW, NBN, GS, XV, HV>, TB * HV, 0) !=
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_conv_dwt<CW, NBN, GS, XV>, TB, 0) !=
             hipSuccess ||
         n < 1)
       n = 1;
@@ -1407,18 +1347,15 @@ int dwt_occ() {
   return occ;
 }
 
-#define OC_DWT_LIST(X)                                                                       \
-  X(false, 16, 1, 4, true, 2) X(false, 16, 2, 4, true, 2) X(false, 16, 4, 4, true, 2)       \
-  X(true, 4, 1, 16, true, 1) X(true, 4, 2, 16, true, 1) X(true, 4, 1, 16, false, 1)          \
-  X(true, 4, 2, 16, false, 1) X(true, 8, 1, 8, true, 1) X(true, 8, 2, 8, true, 1)            \
-  X(true, 8, 1, 8, false, 1) X(true, 8, 2, 8, false, 1) X(true, 16, 1, 4, true, 1)           \
-  X(true, 16, 2, 4, true, 1) X(true, 16, 1, 4, false, 1) X(true, 16, 2, 4, false, 1)
+#define OC_DWT_LIST(X)                                                               \
+  X(4, 1, 16, true) X(4, 2, 16, true) X(4, 1, 16, false) X(4, 2, 16, false)          \
+  X(8, 1, 8, true) X(8, 2, 8, true) X(8, 1, 8, false) X(8, 2, 8, false)              \
+  X(16, 1, 4, true) X(16, 2, 4, true) X(16, 1, 4, false) X(16, 2, 4, false)
 
 int dwt_occupancy(const DwtCfg& c) {
-#define OC_DWT_OCC(FLAT_, CW_, NBN_, GS_, XV_, HV_)                                         \
-  if (c.flat == FLAT_ && c.CW == CW_ && c.NBN == NBN_ && c.GS == GS_ && c.xv == XV_ &&      \
-      c.HV == HV_)                                                                          \
-    return dwt_occ<FLAT_, CW_, NBN_, GS_, XV_, HV_>();
+#define OC_DWT_OCC(CW_, NBN_, GS_, XV_)                                              \
+  if (c.CW == CW_ && c.NBN == NBN_ && c.GS == GS_ && c.xv == XV_)                    \
+    return dwt_occ<CW_, NBN_, GS_, XV_>();
   OC_DWT_LIST(OC_DWT_OCC)
 #undef OC_DWT_OCC
   return 1;
@@ -1426,11 +1363,14 @@ int dwt_occupancy(const DwtCfg& c) {
 
 bool dispatch_dwt(const oc_octree* t, int l, const DwtCfg& c, const float* x, int cin,
                   const float* dy, int cout, float* part, hipStream_t s) {
-#define OC_DWT(FLAT_, CW_, NBN_, GS_, XV_, HV_)                                             \
-  if (c.flat == FLAT_ && c.CW == CW_ && c.NBN == NBN_ && c.GS == GS_ && c.xv == XV_ &&    \
-      c.HV == HV_) {                                                                        \
-    launch_dwt<FLAT_, CW_, NBN_, GS_, XV_, HV_>(t, l, c, x, cin, dy, cout, part, s);      \
-    return true;                                                                          \
+  if (!c.flat) {
+    oc::dws_launch(t, l, c.NBN, c.gchunk, c.nchunks, x, cin, dy, cout, part, s);
+    return true;
+  }
+#define OC_DWT(CW_, NBN_, GS_, XV_)                                                  \
+  if (c.CW == CW_ && c.NBN == NBN_ && c.GS == GS_ && c.xv == XV_) {                  \
+    launch_dwt<CW_, NBN_, GS_, XV_>(t, l, c, x, cin, dy, cout, part, s);             \
+    return true;                                                                     \
   }
   OC_DWT_LIST(OC_DWT)
 #undef OC_DWT
@@ -1510,8 +1450,10 @@ void conv_s1_kernel_name(const oc_octree* t, int l, int K, int cin, int cout, in
   if (pass == 2) {
     DwtCfg d;
     if (pick_dwt(K, t->M[l - 1], cin, cout, &d)) {
-      snprintf(buf, n, "k_conv_dwt<%s, %d, %d, %d, %s, %d>", d.flat ? "true" : "false", d.CW,
-               d.NBN, d.GS, d.xv ? "true" : "false", d.HV);
+      if (d.flat)
+        snprintf(buf, n, "k_conv_dwt<%d, %d, %d, %s>", d.CW, d.NBN, d.GS, d.xv ? "true" : "false");
+      else
+        oc::dws_name(t, l, d.NBN, cin, cout, buf, n);
       return;
     }
     if (sp5_dw_ok(t, l, K, cin, cout)) {

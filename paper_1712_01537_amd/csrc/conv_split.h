@@ -32,4 +32,11 @@ void sp3_launch(const oc_octree* t, int l, const Sp3Cfg& cfg, bool flip, const f
 // Kernel name with template arguments.
 void sp3_name(const Sp3Cfg& cfg, bool flip, bool pooled, char* buf, size_t n);
 
+// Partial sums part[nchunks][27][cin][cout] of the K = 3 weight gradient over
+// chunks of gchunk sibling groups (cin >= 16, cin and cout multiples of 4),
+// nbn = 1 or 2 blocks of 16 columns per workgroup of 16 channels.
+void dws_launch(const oc_octree* t, int l, int nbn, int64_t gchunk, int64_t nchunks, const float* x,
+                int cin, const float* dy, int cout, float* part, hipStream_t s);
+void dws_name(const oc_octree* t, int l, int nbn, int cin, int cout, char* buf, size_t n);
+
 }  // namespace oc

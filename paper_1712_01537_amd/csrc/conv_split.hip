@@ -33,6 +33,18 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const void* p, uint32_t b
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, bytes, 0x00020000);
 }
 
+// Two transposing LDS loads, the second `next` bytes behind the first: the eight
+// rows (two times four) of this lane's channel.
+typedef short v4s __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) v4s lds_v4s;
+__device__ __forceinline__ v4u tr2(const char* p, int next) {
+  const auto* a = (const __attribute__((address_space(3))) char*)p;
+  const v2u lo = __builtin_bit_cast(v2u, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s*)a));
+  const v2u hi =
+      __builtin_bit_cast(v2u, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s*)(a + next)));
+  return v4u{lo[0], lo[1], hi[0], hi[1]};
+}
+
 // ---------------------------------------------------------------------------
 // Stride-1, K = 3 convolution, weights in registers (k_conv_sp3):
 // out[i][n] = sum_k sum_c x[nb(i,k)][c] W'[k][c][n] for the 16-channel chunk
@@ -437,6 +449,308 @@ void launch_sp3(const oc_octree* t, int l, int splits, const float* x, int kk, c
     launch_sp3b<WN, GPB, FLIP, POOL, false>(t, l, splits, x, kk, w, nn, out, relu, part, po, s);
 }
 
+// ---------------------------------------------------------------------------
+// Weight gradient, K = 3, cin >= 16 (k_conv_dws):
+//   dW[k][c][n] = sum over octants i of x[nb(i,k)][c] dY[i][n],
+// products from three bf16 parts.  The MFMA (16x16x32) reduces over the octants
+// of four sibling groups: lane group q = l / 16 supplies the eight children of
+// group q, for A (16 channels) and B (16 columns) alike.  Both are staged as
+// rows of channels and read with transposing LDS loads (ds_read_b64_tr_b16:
+// lane i of a lane group gets channel i of the four rows whose 8-byte quarters
+// the group's lanes name), two per operand part, one per x-bit of the children.
+//
+// A workgroup (chunk, tile) owns 16 channels by 16 NBN columns and a chunk of
+// groups.  It is two halves of four waves; the halves take alternate stages of
+// four groups, each in two LDS buffers of its own, and a half's waves take taps
+// w, w + 4, ...  One barrier per stage: between two of them stage s is
+// multiplied, stage s + 1, loaded a stage earlier, is split and stored, and
+// stage s + 2 is loaded.  Half 0 stores first and half 1 multiplies first, so
+// that each SIMD has one wave of either kind of work.  At the end the halves'
+// sums meet through LDS and go to part[chunk][27 cin][cout].
+//
+// LDS: part p, group g, position (x, y, z) is the 32-byte row 264 p + 66 g +
+// 16 x + 4 y + z; the four rows of a transposing load and those of the next
+// group are then distinct mod 8, which is all 64 banks.  dY: part, group, child
+// rows of 32 NBN bytes, groups padded to the same end.
+//
+// What is not finite is worked out again, wave by wave, with fp32 MFMAs.
+//
+// Measured on an MI355X (before: an fp32 16x16x4 kernel of the same tiles):
+// 16 -> 16 channels on 218768 groups 174 us, 139 TFLOP/s of fp32 products; the
+// whole 24 -> 40 layer of 5 shapes at depth 6, three passes, 224 -> 189 us.
+// With 16 columns the split and store of x, which two halves' waves share with
+// 84 MFMAs each, bound it; with 32 the MFMAs do.
+template <int NBN, bool BIG>
+__global__ __launch_bounds__(TB) __attribute__((amdgpu_waves_per_eu(2))) void k_conv_dws(
+    const int32_t* __restrict__ nbr, int64_t ngroups, int64_t gchunk, const float* __restrict__ x,
+    int cin, const float* __restrict__ dy, int cout, float* __restrict__ part) {
+  constexpr int GS = 4, NJ = 7, HT = TB / 2;  // groups a stage, taps a wave, threads a half
+  constexpr int BN = 16 * NBN;
+  constexpr int XG = 66 * 32, XP = GS * XG;                                // bytes
+  constexpr int YG = 8 * BN * 2 + (NBN == 1 ? 128 : 32), YP = GS * YG;
+  constexpr int BUF = 3 * (XP + YP);
+  constexpr int NRED = NJ * NBN * 4 * 64 * 16;
+  constexpr int NSM = 4 * BUF > NRED ? 4 * BUF : NRED;
+  static_assert(XG % 16 == 0 && YG % 16 == 0 && NSM <= 160 * 1024, "LDS");
+  __shared__ __attribute__((aligned(16))) char smem[NSM];
+
+  const int tid = threadIdx.x & (HT - 1), lane = tid & 63;
+  const int half = __builtin_amdgcn_readfirstlane(threadIdx.x / HT);
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int li = lane & 15, q = lane >> 4;
+  const int nCB = (cin + 15) / 16;
+  const int c0 = 16 * (int)(blockIdx.y % nCB), n0 = BN * (int)(blockIdx.y / nCB);
+  const int64_t gb = (int64_t)blockIdx.x * gchunk;
+  const int64_t ge = gb + gchunk < ngroups ? gb + gchunk : ngroups;
+  if (gb >= ge) return;  // uniform over the workgroup
+  const int ng = (int)(ge - gb);
+  const int nsub = (ng + 2 * GS - 1) / (2 * GS);  // stages of a half
+  char* const mine = smem + half * 2 * BUF;
+
+  const oc::SplitK sk = oc::s3_consts();
+  // x staging: thread -> position, channel quad, every group of the stage
+  const int f = tid & 3, pos = tid >> 2;
+  const int ux = (pos >> 4) - 1, uy = ((pos >> 2) & 3) - 1, uz = (pos & 3) - 1;
+  const int slot = ((ux >> 1) + 1) * 9 + ((uy >> 1) + 1) * 3 + ((uz >> 1) + 1);
+  const int coff = 4 * (ux & 1) + 2 * (uy & 1) + (uz & 1);
+  const int ch = c0 + 4 * f;
+  const int lx = pos * 32 + f * 8;
+  // dY staging: thread -> row of the stage, column quad (8 GS 4 NBN <= HT)
+  const int yr = tid / (4 * NBN), yf = tid % (4 * NBN), yn = n0 + 4 * yf;
+  const bool yon = yr < 8 * GS;
+  const int ly = 3 * XP + (yr >> 3) * YG + (yr & 7) * BN * 2 + yf * 8;
+  // buffer resources relative to the chunk: what lies past it reads as zero
+  const __amdgpu_buffer_rsrc_t rn = rsrc(nbr + 27 * gb, 108u * (uint32_t)ng);
+  const __amdgpu_buffer_rsrc_t rx_ = rsrc(x, BIG ? 0 : (uint32_t)(8 * ngroups * cin * 4));
+  const __amdgpu_buffer_rsrc_t ry_ =
+      rsrc(dy + 8 * gb * cout, BIG ? 0 : (uint32_t)(8 * (int64_t)ng * cout * 4));
+
+  int32_t nb[GS];
+  auto first = [&](int s) { return (2 * s + half) * GS; };  // first group of stage s
+  auto load_nb = [&](int s) {
+#pragma unroll
+    for (int i = 0; i < GS; ++i) {
+      const int g = first(s) + i;  // groups past the chunk: absent
+      const int32_t v = __builtin_amdgcn_raw_buffer_load_b32(rn, 4 * slot, 108 * (g < ng ? g : 0), 0);
+      nb[i] = v;
+    }
+  };
+  v4f rx[GS], ry;
+  auto load = [&](int s) {
+#pragma unroll
+    for (int i = 0; i < GS; ++i) {
+      const bool live = first(s) + i < ng && nb[i] >= 0 && ch < cin;
+      if constexpr (BIG) {
+        rx[i] = v4f{0.f, 0.f, 0.f, 0.f};
+        if (live) rx[i] = *reinterpret_cast<const v4f*>(x + (int64_t)(nb[i] + coff) * cin + ch);
+      } else {
+        const uint32_t off = (uint32_t)(nb[i] + coff) * (uint32_t)(4 * cin) + 4 * ch;
+        rx[i] = __builtin_bit_cast(
+            v4f, __builtin_amdgcn_raw_buffer_load_b128(rx_, live ? off : ~0u, 0, 0));
+      }
+    }
+    const bool live = yon && first(s) + (yr >> 3) < ng && yn < cout;
+    if constexpr (BIG) {
+      ry = v4f{0.f, 0.f, 0.f, 0.f};
+      if (live)
+        ry = *reinterpret_cast<const v4f*>(dy + (8 * (gb + first(s)) + yr) * (int64_t)cout + yn);
+    } else {
+      const uint32_t off = (uint32_t)(8 * first(s) + yr) * (uint32_t)(4 * cout) + 4 * yn;
+      ry = __builtin_bit_cast(
+          v4f, __builtin_amdgcn_raw_buffer_load_b128(ry_, live ? off : ~0u, 0, 0));
+    }
+  };
+  auto store = [&](int s) {
+    char* b = mine + (s & 1) * BUF;
+#pragma unroll
+    for (int i = 0; i < GS; ++i) {
+      v2u p[3];
+      oc::s3_split4(sk, rx[i], p);
+#pragma unroll
+      for (int k = 0; k < 3; ++k) *reinterpret_cast<v2u*>(b + lx + k * XP + i * XG) = p[k];
+    }
+    if (yon) {
+      v2u p[3];
+      oc::s3_split4(sk, half ? -ry : ry, p);
+#pragma unroll
+      for (int k = 0; k < 3; ++k) *reinterpret_cast<v2u*>(b + ly + k * YP) = p[k];
+    }
+  };
+
+  // reads: lane li names the 8-byte quarter li & 3 of row (child) 4 hh + (li >> 2)
+  const int r4 = li >> 2, tq = li & 3;
+  int ax[NJ];
+#pragma unroll
+  for (int j = 0; j < NJ; ++j) {
+    const int tap = wave + 4 * j < 27 ? wave + 4 * j : 0;
+    ax[j] = q * XG + tq * 8 + 32 * (16 * (tap / 9) + 4 * (tap / 3 % 3 + (r4 >> 1)) + tap % 3 + (r4 & 1));
+  }
+  const int by = 3 * XP + q * YG + r4 * BN * 2 + tq * 8;
+  v4f acc[NJ][NBN];
+#pragma unroll
+  for (int j = 0; j < NJ; ++j)
+#pragma unroll
+    for (int n = 0; n < NBN; ++n) acc[j][n] = v4f{0.f, 0.f, 0.f, 0.f};
+
+  // P taps a unit, so that two sums at least are in turn; the reads of the
+  // next unit are issued before a unit's MFMAs.  A stage's six products are
+  // summed from zero and then added to the running sum, which is rounded once
+  // a stage that way, to nearest: the MFMA adding all six to it was measured to
+  // leave six times the fp32 kernel's error (3.8e-6 of dW at 218768 groups, 16 ->
+  // 16).  The MFMA itself cuts its sums off, always downwards it seems: with dY
+  // as it is in both halves, 1.5e-6 was left, growing with the octants as a bias
+  // does.  Half 1 therefore takes -dY, so that the two halves' biases cancel.  (Tap 27 of wave 3 reads tap
+  // 0's rows; its sum is dropped.)
+  auto multiply = [&](int s) {
+    constexpr int P = NBN == 1 ? 2 : 1, U = (NJ + P - 1) / P;
+    const char* b = mine + (s & 1) * BUF;
+    v4u bq[NBN][3], a[2][P][3];
+#pragma unroll
+    for (int n = 0; n < NBN; ++n)
+#pragma unroll
+      for (int k = 0; k < 3; ++k)
+        bq[n][k] = tr2(b + by + k * YP + n * 32, 4 * BN * 2);
+    auto rd = [&](int u) {
+#pragma unroll
+      for (int i = 0; i < P; ++i)
+        if (u * P + i < NJ) {
+#pragma unroll
+          for (int k = 0; k < 3; ++k) a[u & 1][i][k] = tr2(b + ax[u * P + i] + k * XP, 16 * 32);
+        }
+    };
+    v4f t[2][P][NBN];
+    auto add = [&](int u) {
+#pragma unroll
+      for (int r = 0; r < P; ++r)
+        if (u * P + r < NJ) {
+#pragma unroll
+          for (int n = 0; n < NBN; ++n) acc[u * P + r][n] += t[u & 1][r][n];
+        }
+    };
+    rd(0);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (u + 1 < U) rd(u + 1);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int i = 0; i < 6; ++i)
+#pragma unroll
+        for (int r = 0; r < P; ++r)
+          if (u * P + r < NJ) {
+#pragma unroll
+            for (int n = 0; n < NBN; ++n)
+              t[u & 1][r][n] = oc::s3_product(i, a[u & 1][r], bq[n],
+                                              i == 0 ? v4f{0.f, 0.f, 0.f, 0.f} : t[u & 1][r][n]);
+          }
+      if (u > 0) add(u - 1);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    add(U - 1);
+  };
+
+  load_nb(0);
+  load(0);
+  load_nb(1);
+  store(0);
+  load(1);
+  load_nb(2);
+  auto stage = [&](int s) {  // stage s to LDS, s + 1 on its way
+    if (s >= nsub) return;
+    store(s);
+    load(s + 1);
+    load_nb(s + 2);
+  };
+  for (int s = 0; s < nsub; ++s) {
+    lds_barrier();
+    if (half == 0) {
+      stage(s + 1);
+      multiply(s);
+    } else {
+      multiply(s);
+      stage(s + 1);
+    }
+  }
+
+  bool bad = false;
+#pragma unroll
+  for (int j = 0; j < NJ; ++j)
+#pragma unroll
+    for (int n = 0; n < NBN; ++n) bad |= oc::s3_bad(acc[j][n]);
+  if (__builtin_expect(__any(bad), 0)) {  // this wave's sums again, in plain fp32
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+      for (int n = 0; n < NBN; ++n) acc[j][n] = v4f{0.f, 0.f, 0.f, 0.f};
+    for (int s = 0; s < nsub; ++s)
+      for (int i = 0; i < 2 * GS; ++i) {
+        const int gl = first(s) + (i >> 1);
+        if (gl >= ng) break;
+        const int64_t g = gb + gl;
+        const int c = 4 * (i & 1) + q;  // the lane group's child
+        float bv[NBN];
+#pragma unroll
+        for (int n = 0; n < NBN; ++n) {
+          const int col = n0 + 16 * n + li;
+          bv[n] = col < cout ? dy[(8 * g + c) * cout + col] : 0.f;
+        }
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+          const int tap = wave + 4 * j < 27 ? wave + 4 * j : 0;
+          const int vx = (c >> 2) + tap / 9 - 1, vy = ((c >> 1) & 1) + tap / 3 % 3 - 1,
+                    vz = (c & 1) + tap % 3 - 1;
+          const int32_t e = nbr[27 * g + ((vx >> 1) + 1) * 9 + ((vy >> 1) + 1) * 3 + (vz >> 1) + 1];
+          const int64_t row = (int64_t)e + 4 * (vx & 1) + 2 * (vy & 1) + (vz & 1);
+          const float av = e >= 0 && c0 + li < cin ? x[row * cin + c0 + li] : 0.f;
+#pragma unroll
+          for (int n = 0; n < NBN; ++n)
+            acc[j][n] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, bv[n], acc[j][n], 0, 0, 0);
+        }
+      }
+  } else if (half) {
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+      for (int n = 0; n < NBN; ++n) acc[j][n] = -acc[j][n];
+  }
+
+  // halves add their sums: tap j goes to half j < JH ? 0 : 1
+  constexpr int JH = (NJ + 1) / 2;
+  v4f* red = reinterpret_cast<v4f*>(smem);
+  __syncthreads();  // the last stage's LDS reads are done
+#pragma unroll
+  for (int j = 0; j < NJ; ++j)
+    if ((j < JH) != (half == 0))
+#pragma unroll
+      for (int n = 0; n < NBN; ++n) red[((j * NBN + n) * 4 + wave) * 64 + lane] = acc[j][n];
+  __syncthreads();
+  float* pp = part + (int64_t)blockIdx.x * 27 * cin * cout;
+#pragma unroll
+  for (int j = 0; j < NJ; ++j) {
+    const int tap = wave + 4 * j;
+    if (tap >= 27 || (j < JH) != (half == 0)) continue;
+#pragma unroll
+    for (int n = 0; n < NBN; ++n) {
+      const v4f v = acc[j][n] + red[((j * NBN + n) * 4 + wave) * 64 + lane];
+      const int col = n0 + 16 * n + li;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {  // row 4 q + r of the product: the channel
+        const int c = c0 + 4 * q + r;
+        if (c < cin && col < cout) pp[((int64_t)tap * cin + c) * cout + col] = v[r];
+      }
+    }
+  }
+}
+
+template <int NBN>
+void launch_dws(const oc_octree* t, int l, int64_t gchunk, int64_t nchunks, const float* x,
+                int cin, const float* dy, int cout, float* part, hipStream_t s) {
+  const bool big = t->N[l] * std::max(cin, cout) * 4 >= int64_t(1) << 32;
+  const auto kernel = big ? k_conv_dws<NBN, true> : k_conv_dws<NBN, false>;
+  const dim3 grid((unsigned)nchunks, (unsigned)(oc::cdiv(cin, 16) * oc::cdiv(cout, 16 * NBN)));
+  oc::launch_main(kernel, grid, dim3(TB), s, (const int32_t*)t->nbr[l], t->M[l - 1], gchunk, x, cin,
+                  dy, cout, part);
+}
+
 }  // namespace
 
 namespace oc {
@@ -484,6 +798,19 @@ void sp3_launch(const oc_octree* t, int l, const Sp3Cfg& c, bool flip, const flo
 void sp3_name(const Sp3Cfg& c, bool flip, bool pooled, char* buf, size_t n) {
   snprintf(buf, n, "k_conv_sp3<%d, %d, %s, %s>", c.wn, c.gpb, flip ? "true" : "false",
            pooled && c.splits == 1 ? "true" : "false");
+}
+
+void dws_launch(const oc_octree* t, int l, int nbn, int64_t gchunk, int64_t nchunks, const float* x,
+                int cin, const float* dy, int cout, float* part, hipStream_t s) {
+  if (nbn == 1)
+    launch_dws<1>(t, l, gchunk, nchunks, x, cin, dy, cout, part, s);
+  else
+    launch_dws<2>(t, l, gchunk, nchunks, x, cin, dy, cout, part, s);
+}
+
+void dws_name(const oc_octree* t, int l, int nbn, int cin, int cout, char* buf, size_t n) {
+  snprintf(buf, n, "k_conv_dws<%d, %s>", nbn,
+           t->N[l] * std::max(cin, cout) * 4 >= int64_t(1) << 32 ? "true" : "false");
 }
 
 }  // namespace oc
