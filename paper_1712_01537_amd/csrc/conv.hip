@@ -445,8 +445,8 @@ oc_status oc_conv_dw_partials(const oc_octree* t, int32_t l, int32_t K, int32_t 
   // strided and native-bf16 layers, and layers without groups, write dw directly
   if (stride > 1 || bf16_native(sh, dt, cin, cout) || sh.units == 0) return OC_OK;
   // oc_conv_bwd's stride-1 workspace: (bf16: widened w and x,) the masked dy,
-  // then the weight gradient's partial sums
-  size_t off = mask_ws_bytes(sh, cout);
+  // then the weight gradient's workspace
+  size_t off = mask_ws_bytes(sh, cout) + oc::conv_s1_dw_offset(t, l, K, cin, cout);
   if (dt == OC_BF16) off += w32_bytes(sh, cin, cout) + x32_bytes(sh, cin);
   *offset = off;
   *nparts = (int32_t)oc::conv_s1_dw_parts(t, l, K, cin, cout);

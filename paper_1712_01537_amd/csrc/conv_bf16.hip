@@ -290,18 +290,13 @@ __global__ __launch_bounds__(TB) void k_bf_cvt_g(const float* __restrict__ in,
 }
 
 // out[e] = sum_{r < nparts} part[r][e] in the order r = 0, 1, ... (n % 4 == 0).
-// gate != NULL: only when *gate is set; bad != NULL: *bad = 1 when a sum is
-// infinite or NaN.
 __global__ __launch_bounds__(TB) void k_bf_sum(const float* __restrict__ part, int nparts,
-                                               int64_t n, float* __restrict__ out,
-                                               const uint32_t* __restrict__ gate, uint32_t* bad) {
-  if (gate && *gate == 0) return;
+                                               int64_t n, float* __restrict__ out) {
   const int64_t e = 4 * ((int64_t)blockIdx.x * TB + threadIdx.x);
   if (e >= n) return;
   v4f s = {0.f, 0.f, 0.f, 0.f};
   for (int r = 0; r < nparts; ++r) s += *reinterpret_cast<const v4f*>(part + r * n + e);
   *reinterpret_cast<v4f*>(out + e) = s;
-  if (bad && oc::s3_bad(s)) *bad = 1;
 }
 
 // ---------------------------------------------------------------------------
@@ -927,13 +922,14 @@ __global__ __launch_bounds__(NW_ * 64, 8 / NW_) void k_conv_bfw(const int32_t* _
 // dyg [ngroups][cout][8] bf16; part [nranges][K^3][cin][cout].
 // SP: fp32 operands in three bf16 parts (x [8 ngroups][3 cin], dyg
 // [3][ngroups][cout][8]); a range is walked once for each of the six products,
-// the sums staying in registers.
+// the sums staying in registers; *bad = 1 when one of them is infinite or NaN.
 template <int K, int MAXC, int NW, int GS, bool SP>
 __global__ __launch_bounds__(NW * 64, 8 / NW) void k_conv_bf_dw(const int32_t* __restrict__ nbr,
                                                       int64_t ngroups,
                                                       const uint16_t* __restrict__ x, int cin,
                                                       const uint16_t* __restrict__ dyg, int cout,
-                                                      int nranges, float* __restrict__ part) {
+                                                      int nranges, float* __restrict__ part,
+                                                      uint32_t* bad) {
   constexpr int R = (K - 1) / 2, S = K + 1, K3 = K * K * K;
   constexpr int NU = K == 5 ? 13 : 3;        // units
   static_assert(GS % 4 == 0 && NW * MAXC >= (K == 5 ? 40 : 36), "tile");
@@ -1203,6 +1199,7 @@ __global__ __launch_bounds__(NW * 64, 8 / NW) void k_conv_bf_dw(const int32_t* _
       for (int nb = 0; nb < 4; ++nb) {
         const int n = n0 + 16 * nb + li;
         if (n < cout) {
+          if (SP && oc::s3_bad(acc[mi][nb])) *bad = 1;
 #pragma unroll
           for (int j = 0; j < 4; ++j)
             dst[(int64_t)(c0 + 16 * cb + 4 * q + j) * cout + n] = acc[mi][nb][j];
@@ -1364,13 +1361,12 @@ void conv_bf16_bwd(const oc_octree* t, int l, int K, const uint16_t* x, int cin,
     const dim3 grid((unsigned)dw_items(K, nr), blocks(cout, 64), blocks(cin, 64));
     if (K == 5)
       launch_main((k_conv_bf_dw<5, 10, 4, 4, false>), grid, dim3(256), s, (const int32_t*)t->nbr[l], G, x,
-                  cin, dyg, cout, nr, part);
+                  cin, dyg, cout, nr, part, (uint32_t*)nullptr);
     else
       launch_main((k_conv_bf_dw<3, 5, 8, 8, false>), grid, dim3(512), s, (const int32_t*)t->nbr[l], G, x,
-                  cin, dyg, cout, nr, part);
+                  cin, dyg, cout, nr, part, (uint32_t*)nullptr);
     const int64_t E = (int64_t)K3 * cin * cout;
-    oc::launch(k_bf_sum, dim3(blocks(E, 4 * TB)), dim3(TB), 0, s, part, nr, E, dw,
-               (const uint32_t*)nullptr, (uint32_t*)nullptr);
+    oc::launch(k_bf_sum, dim3(blocks(E, 4 * TB)), dim3(TB), 0, s, part, nr, E, dw);
   }
 }
 
@@ -1427,33 +1423,28 @@ bool sp5_dw_ok(const oc_octree* t, int l, int K, int cin, int cout) {
          cdiv(t->M[l - 1], 8) >= cu_count();
 }
 
-size_t sp5_dw_ws(const oc_octree* t, int l, int cin, int cout) {
-  return 256 + align256((size_t)t->N[l] * cin * 6) + align256((size_t)t->N[l] * cout * 6) +
-         (size_t)dw_ranges(t, l, 5, cin, cout) * 125 * cin * cout * sizeof(float);
+size_t sp5_dw_parts(const oc_octree* t, int l, int cin, int cout) {
+  return (size_t)dw_ranges(t, l, 5, cin, cout);
+}
+
+size_t sp5_dw_offset(const oc_octree* t, int l, int cin, int cout) {
+  return 256 + align256((size_t)t->N[l] * cin * 6) + align256((size_t)t->N[l] * cout * 6);
 }
 
 uint32_t* sp5_dw(const oc_octree* t, int l, const float* x, int cin, const float* dy, int cout,
-                 float* dw, void* ws, hipStream_t s) {
-  const int64_t G = t->M[l - 1], N = t->N[l], E = (int64_t)125 * cin * cout;
+                 void* ws, hipStream_t s) {
+  const int64_t G = t->M[l - 1], N = t->N[l];
   uint32_t* flag = (uint32_t*)ws;
   uint16_t* x3 = (uint16_t*)((char*)ws + 256);
   uint16_t* dyg = (uint16_t*)((char*)x3 + align256((size_t)N * cin * 6));
-  float* part = (float*)((char*)dyg + align256((size_t)N * cout * 6));
+  float* part = (float*)((char*)ws + sp5_dw_offset(t, l, cin, cout));
   sp_rows(x, N, cin, x3, s);
   oc::launch(k_sp_cvt_g, dim3(blocks(G * cout, TB)), dim3(TB), 0, s, dy, G, cout, dyg, flag);
   const int nr = dw_ranges(t, l, 5, cin, cout);
   const dim3 grid((unsigned)dw_items(5, nr), blocks(cout, 64), blocks(cin, 64));
   launch_main((k_conv_bf_dw<5, 10, 4, 4, true>), grid, dim3(256), s, (const int32_t*)t->nbr[l], G,
-              (const uint16_t*)x3, cin, (const uint16_t*)dyg, cout, nr, part);
-  oc::launch(k_bf_sum, dim3(blocks(E, 4 * TB)), dim3(TB), 0, s, (const float*)part, nr, E, dw,
-             (const uint32_t*)nullptr, flag);
+              (const uint16_t*)x3, cin, (const uint16_t*)dyg, cout, nr, part, flag);
   return flag;
-}
-
-void sp5_sum_gated(const float* part, int nparts, int64_t n, float* out, const uint32_t* gate,
-                   hipStream_t s) {
-  oc::launch(k_bf_sum, dim3(blocks(n, 4 * TB)), dim3(TB), 0, s, part, nparts, n, out, gate,
-             (uint32_t*)nullptr);
 }
 
 void sp5_dw_name(char* buf, size_t n) { snprintf(buf, n, "k_conv_bf_dw<5, 10, 4, 4, true>"); }

@@ -51,18 +51,20 @@ void conv_s1_bwd_data_pool_f32(const oc_octree* t, int l, int K, const float* dy
                                const float* w, int cin, float* dx, const float* mask,
                                const uint8_t* sw, float* dxf, float* ws, hipStream_t s);
 
-// Number of [K^3][cin][cout] fp32 partial sums conv_s1_bwd_weight_f32 needs.
+// Number of [K^3][cin][cout] fp32 partial sums of conv_s1_bwd_weight_f32, and
+// where they start in its workspace (bytes; ahead of them what the kernel on
+// three bf16 parts takes).
 size_t conv_s1_dw_parts(const oc_octree* t, int l, int K, int cin, int cout);
+size_t conv_s1_dw_offset(const oc_octree* t, int l, int K, int cin, int cout);
 
-// Bytes of workspace conv_s1_bwd_weight_f32 needs: the partial sums, or what
-// the kernel on three bf16 parts takes.
+// Bytes of workspace conv_s1_bwd_weight_f32 needs.
 size_t conv_s1_dw_ws(const oc_octree* t, int l, int K, int cin, int cout);
 
-// dw [K^3][cin][cout] = weight gradient of a stride-1 convolution; part:
-// conv_s1_dw_ws() bytes.  defer: leave the partial sums in part
-// (dw not written), for a later sum_partials_multi.
+// dw [K^3][cin][cout] = weight gradient of a stride-1 convolution; ws:
+// conv_s1_dw_ws() bytes.  defer: leave the partial sums in ws (dw not
+// written), for a later sum_partials_multi.
 void conv_s1_bwd_weight_f32(const oc_octree* t, int l, int K, const float* x, int cin,
-                            const float* dy, int cout, float* dw, float* part, hipStream_t s,
+                            const float* dy, int cout, float* dw, float* ws, hipStream_t s,
                             bool defer = false);
 
 // outs[i] = fixed-order sum of nparts[i] partials of counts[i] fp32 entries at

@@ -1552,21 +1552,27 @@ size_t conv_s1_dw_parts(const oc_octree* t, int l, int K, int cin, int cout) {
   int64_t np;
   if (pick_dwt(K, t->M[l - 1], cin, cout, &d)) {
     np = d.nchunks;
+  } else if (sp5_dw_ok(t, l, K, cin, cout)) {
+    np = sp5_dw_parts(t, l, cin, cout);
   } else {
     np = pick_dw(K, t->M[l - 1], cin, cout).nchunks;
   }
   return (size_t)np;
 }
 
+size_t conv_s1_dw_offset(const oc_octree* t, int l, int K, int cin, int cout) {
+  return sp5_dw_ok(t, l, K, cin, cout) ? sp5_dw_offset(t, l, cin, cout) : 0;
+}
+
 size_t conv_s1_dw_ws(const oc_octree* t, int l, int K, int cin, int cout) {
-  const size_t parts = conv_s1_dw_parts(t, l, K, cin, cout) * K * K * K * cin * cout * sizeof(float);
-  if (!sp5_dw_ok(t, l, K, cin, cout)) return parts;
-  return std::max(256 + parts, sp5_dw_ws(t, l, cin, cout));  // 256: the flag
+  return conv_s1_dw_offset(t, l, K, cin, cout) +
+         conv_s1_dw_parts(t, l, K, cin, cout) * K * K * K * cin * cout * sizeof(float);
 }
 
 void conv_s1_bwd_weight_f32(const oc_octree* t, int l, int K, const float* x, int cin,
-                            const float* dy, int cout, float* dw, float* part,
+                            const float* dy, int cout, float* dw, float* ws,
                             hipStream_t s, bool defer) {
+  float* part = (float*)((char*)ws + conv_s1_dw_offset(t, l, K, cin, cout));
   const int64_t entries = (int64_t)K * K * K * cin * cout;
   if (conv_cin_supported(K, cin, cout)) {
     conv_cin_dw(t, l, x, cin, dy, cout, dw, part, s, defer);
@@ -1581,13 +1587,13 @@ void conv_s1_bwd_weight_f32(const oc_octree* t, int l, int K, const float* x, in
     }
     return;
   }
-  const DwCfg c = pick_dw(K, t->M[l - 1], cin, cout);
-  // (deferred sums are the fp32 kernel's: oc_conv_dw_partials names their number)
+  DwCfg c = pick_dw(K, t->M[l - 1], cin, cout);
   const uint32_t* gate = nullptr;
-  if (!defer && oc::sp5_dw_ok(t, l, K, cin, cout) && (uintptr_t)dw % 16 == 0) {
-    // the launch below then works out again what is not finite
-    gate = oc::sp5_dw(t, l, x, cin, dy, cout, dw, part, s);
-    part += 64;  // behind the flag
+  if (sp5_dw_ok(t, l, K, cin, cout)) {
+    // the launch below forms the same partial sums again when one is not finite
+    gate = sp5_dw(t, l, x, cin, dy, cout, ws, s);
+    c.nchunks = (int64_t)sp5_dw_parts(t, l, cin, cout);
+    c.gchunk = oc::cdiv(t->M[l - 1], c.nchunks);
   }
 #define OC_DW(K_, VA_, VB_, TT_, MB_)                                                       \
   if (K == K_ && c.VA == VA_ && c.VB == VB_ && c.TT == TT_ && c.MB == MB_) {               \
@@ -1611,10 +1617,7 @@ void conv_s1_bwd_weight_f32(const oc_octree* t, int l, int K, const float* x, in
     oc::set_error("no weight-gradient kernel for K=%d cin=%d cout=%d", K, cin, cout);
   }
 #undef OC_DW
-  if (gate)
-    oc::sp5_sum_gated(part, (int)c.nchunks, entries, dw, gate, s);
-  else if (!defer)
-    sum_parts(part, (int)c.nchunks, entries, dw, s);
+  if (!defer) sum_parts(part, (int)c.nchunks, entries, dw, s);
 }
 
 void sum_partials(const float* part, int np, int64_t n, float* out, hipStream_t s) {

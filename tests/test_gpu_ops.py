@@ -260,6 +260,34 @@ def test_conv_k5_split_parts(seed, B, n, depth, cin, cout, on):
         assert float((g[ok] - r[ok]).abs().max()) <= tol, (tag, tol)
 
 
+def _k5_layer(cin, cout, seed=311):
+    """A tree with a tile per compute unit, and one K = 5 layer's operands."""
+    oc = _oc()
+    pts, nrm, offs = synth.random_cloud(seed, 7, 6000, "union")
+    tree = oc.oc_build(torch.as_tensor(pts).cuda(), torch.as_tensor(nrm).cuda(), offs, 6, 2)
+    g = torch.Generator("cuda").manual_seed(seed)
+    N = tree.num(6)
+    assert N >= 64 * torch.cuda.get_device_properties(0).multi_processor_count
+    return (oc, tree, torch.randn((N, cin), generator=g, device="cuda"),
+            torch.randn((125, cin, cout), generator=g, device="cuda") / math.sqrt(125 * cin),
+            torch.randn((N, cout), generator=g, device="cuda"))
+
+
+@pytest.mark.parametrize("cin,cout,value", [(64, 64, 0.5), (128, 64, float("inf"))])
+def test_conv_k5_deferred_dw(cin, cout, value):
+    """The deferred weight gradient of a K = 5 fp32 layer on three bf16 parts
+    has the bits of the direct one, also where some of it is not finite."""
+    oc, tree, x, w, dy = _k5_layer(cin, cout)
+    x[77, 3] = value
+    pending = []
+    _, want = oc.oc_conv_bwd(tree, 6, 5, 1, x, w, dy, need_dx=False)
+    _, got = oc.oc_conv_bwd(tree, 6, 5, 1, x, w, dy, need_dx=False, defer=pending)
+    assert len(pending) == 1
+    oc.oc_sum_partials(pending)
+    assert bool(want.isfinite().all()) == math.isfinite(value)
+    assert torch.equal(want.view(torch.int32), got.view(torch.int32))
+
+
 SR_SMALL = [  # seed, B, n, depth, stride, cin, cout, relu, bf16
     (101, 2, 400, 4, 4, 5, 7, False, False),
     (102, 3, 600, 5, 4, 16, 32, True, False),
