@@ -45,10 +45,10 @@ void round_bf16(const float* x, int64_t n, uint16_t* y, hipStream_t s);
 // gradient, kk = cout, nn = cin) and returns a flag in ws (sp5_fwd_ws bytes)
 // that the GPU sets when an output is infinite or NaN: the split has no such
 // values, so the caller then computes the layer again with the fp32 kernel,
-// gated on the flag.  out 16-byte aligned.  sp5_dw: the weight gradient's
-// sp5_dw_parts partial sums [125][cin][cout], sp5_dw_offset bytes into ws,
-// and the flag, set when one of them is not finite (the caller then has the
-// fp32 kernel form all of them again).
+// gated on the flag.  sp5_dw: the weight gradient's sp5_dw_parts partial sums
+// [125][cin][cout], sp5_dw_offset bytes into ws, and the flag, set when one of
+// them is not finite (the caller then has the fp32 kernel form all of them
+// again).
 bool sp5_fwd_ok(const oc_octree* t, int l, int K, int kk, int nn);
 size_t sp5_fwd_ws(const oc_octree* t, int l, int kk, int nn);
 uint32_t* sp5_fwd(const oc_octree* t, int l, bool flip, const float* x, int kk, const float* w,

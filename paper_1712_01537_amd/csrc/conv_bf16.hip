@@ -48,6 +48,7 @@
 namespace {
 
 typedef float v4f __attribute__((ext_vector_type(4)));
+typedef float v4fu __attribute__((ext_vector_type(4), aligned(4)));  // of any fp32 buffer
 typedef uint32_t v4u __attribute__((ext_vector_type(4)));
 typedef short v4s __attribute__((ext_vector_type(4)));
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
@@ -881,8 +882,8 @@ __global__ __launch_bounds__(NW_ * 64, 8 / NW_) void k_conv_bfw(const int32_t* _
     const int n = n0 + cq;
     v4f sum = *reinterpret_cast<const v4f*>(&red[r * RS + cq]);
     if (row < nrows && n < nn) {
-      v4f* dst = reinterpret_cast<v4f*>(out + row * nn + n);
-      if (acc_in) sum = *dst + sum;
+      v4fu* dst = reinterpret_cast<v4fu*>(out + row * nn + n);
+      if (acc_in) sum = (v4f)*dst + sum;
       if (SP && oc::s3_bad(sum)) *bad = 1;
       if (relu) {
 #pragma unroll

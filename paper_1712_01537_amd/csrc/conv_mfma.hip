@@ -1263,7 +1263,7 @@ void dispatch_tile(const oc_octree* t, int l, int K, const float* x, int kk, con
                    const RouteOut* ro = nullptr) {
   TileCfg c = pick_tile(K, t->M[l - 1], kk, nn);
   const uint32_t* gate = nullptr;
-  if (oc::sp5_fwd_ok(t, l, K, kk, nn) && (uintptr_t)out % 16 == 0) {
+  if (oc::sp5_fwd_ok(t, l, K, kk, nn)) {
     // the launch below then works out again, in one split, what is not finite
     gate = oc::sp5_fwd(t, l, FLIP, x, kk, w, nn, out, relu, part, s);
     c.splits = 1;

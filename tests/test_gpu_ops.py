@@ -288,6 +288,37 @@ def test_conv_k5_deferred_dw(cin, cout, value):
     assert torch.equal(want.view(torch.int32), got.view(torch.int32))
 
 
+def test_conv_k5_unaligned_buffers():
+    """Buffers off 16 bytes give a K = 5 fp32 layer on three bf16 parts the bits
+    of aligned ones, in each pass."""
+    oc, tree, x, w, dy = _k5_layer(64, 64)
+
+    def at(off, t=None, shape=None):  # t's copy, or NaN, `off` floats into a buffer
+        n = math.prod(shape or t.shape)
+        v = torch.full((n + 4,), float("nan"), device="cuda")[off:off + n].view(shape or t.shape)
+        return v if t is None else v.copy_(t)
+
+    def run(off):
+        xo, wo, dyo = at(off, x), at(off, w), at(off, dy)
+        y, dx, dw = (at(off, None, t.shape) for t in (x, x, w))
+        L, p = oc.load(), lambda t: t.data_ptr()
+        sz = max(f(tree.handle, 6, 5, 1, 0, 64, 64)
+                 for f in (L.oc_conv_fwd_workspace, L.oc_conv_bwd_workspace))
+        ws = torch.empty(sz, dtype=torch.uint8, device="cuda")
+        s = torch.cuda.current_stream().cuda_stream
+        assert L.oc_conv_fwd(tree.handle, 6, 5, 1, 0, p(xo), 64, p(wo), 64, p(y), p(ws), sz, 0, s) == 0
+        assert L.oc_conv_bwd(tree.handle, 6, 5, 1, 0, p(xo), 64, p(wo), 64, None, p(dyo), p(dx),
+                             p(dw), p(ws), sz, 0, s) == 0
+        torch.cuda.synchronize()
+        return y, dx, dw
+
+    for tag, a, b in zip(("y", "dx", "dw"), run(0), run(1)):
+        if tag == "dw":  # its partial sums are added in another order, as for any layer
+            assert float((a - b).norm()) <= 1e-6 * float(a.norm())
+        else:
+            assert torch.equal(a.view(torch.int32), b.view(torch.int32)), tag
+
+
 SR_SMALL = [  # seed, B, n, depth, stride, cin, cout, relu, bf16
     (101, 2, 400, 4, 4, 5, 7, False, False),
     (102, 3, 600, 5, 4, 16, 32, True, False),
