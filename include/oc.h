@@ -248,8 +248,11 @@ oc_status oc_conv_pool_fwd(const oc_octree* tree, int32_t depth, int32_t ksize, 
  * library, 32 MiB per device, held from the first call on a device until the
  * process ends; the call allocates nothing.  Arguments as oc_conv_fwd.
  * Returns OC_ERR_UNSUPPORTED when the call would need more workspace than
- * 32 MiB (oc_conv_fwd_workspace tells) and for strides other than 1.
- * Results are identical, bit for bit, to oc_conv_fwd's.  Every call on a
+ * 32 MiB and for strides other than 1.  Results are identical, bit for bit,
+ * to oc_conv_fwd's where oc_conv_fwd_workspace is at most 32 MiB.  Above that
+ * a ksize 5 fp32 layer on three bf16 parts runs on the fp32 kernel, which
+ * needs less and whose sums are rounded otherwise (within the same error);
+ * other layers are refused.  Every call on a
  * device shares that device's array: calls that overlap on one device (other
  * streams, other threads) race and must be ordered by the caller. */
 oc_status oc_conv_fwd_noalloc(const oc_octree* tree, int32_t depth, int32_t ksize, int32_t stride,

@@ -48,6 +48,15 @@ oc_status check_tree_level(const oc_octree* t, int32_t l, int32_t min_l);
 oc_status conv_check(const oc_octree* t, int32_t l, int32_t K, int32_t stride, oc_dtype dt,
                      int32_t cin, int32_t cout, const char* who);
 
+// oc_conv_fwd and the workspace it needs.  parts3 false: without the K = 5 fp32
+// kernel on three bf16 parts, whose copies of x and w in parts are most of that
+// workspace; the fp32 kernel takes its layers.
+size_t conv_fwd_ws(const oc_octree* t, int32_t l, int32_t K, int32_t stride, oc_dtype dt,
+                   int32_t cin, int32_t cout, bool parts3);
+oc_status conv_fwd(const oc_octree* t, int32_t l, int32_t K, int32_t stride, oc_dtype dt,
+                   const void* x, int32_t cin, const void* w, int32_t cout, float* y, void* ws,
+                   size_t ws_bytes, int32_t flags, bool parts3, hipStream_t s);
+
 // Compute units of the current device (cached per device).
 int cu_count();
 

@@ -136,11 +136,11 @@ bool bf16_native(const ConvShape& sh, oc_dtype dt, int cin, int cout) {
 }
 
 size_t fwd_ws_bytes(const oc_octree* t, int32_t l, const ConvShape& sh, oc_dtype dt, int cin,
-                    int cout) {
+                    int cout, bool parts3 = true) {
   if (sh.stride > 1) return oc::conv_s2_fwd_ws(t, l, sh.r, cin, cout, dt == OC_BF16);
   if (sh.n_in == 0) return 0;
   if (bf16_native(sh, dt, cin, cout)) return oc::conv_bf16_fwd_ws(sh.K, cin, cout);
-  const size_t tile = oc::conv_s1_tile_ws(t, l, sh.K, cin, cout);
+  const size_t tile = oc::conv_s1_tile_ws(t, l, sh.K, cin, cout, parts3);
   return dt == OC_F32 ? tile : x32_bytes(sh, cin) + w32_bytes(sh, cin, cout) + tile;
 }
 
@@ -198,6 +198,51 @@ oc_status oc::conv_check(const oc_octree* t, int32_t l, int32_t K, int32_t strid
   return check_conv(t, l, K, stride, dt, cin, cout, &sh, who);
 }
 
+size_t oc::conv_fwd_ws(const oc_octree* t, int32_t l, int32_t K, int32_t stride, oc_dtype dt,
+                       int32_t cin, int32_t cout, bool parts3) {
+  ConvShape sh;
+  if (check_conv(t, l, K, stride, dt, cin, cout, &sh, "oc_conv_fwd_workspace") != OC_OK) return 0;
+  return fwd_ws_bytes(t, l, sh, dt, cin, cout, parts3);
+}
+
+oc_status oc::conv_fwd(const oc_octree* t, int32_t l, int32_t K, int32_t stride, oc_dtype dt,
+                       const void* x, int32_t cin, const void* w, int32_t cout, float* y,
+                       void* ws, size_t ws_bytes, int32_t flags, bool parts3, hipStream_t s) {
+  ConvShape sh;
+  oc_status st = check_conv(t, l, K, stride, dt, cin, cout, &sh, "oc_conv_fwd");
+  if (st != OC_OK) return st;
+  if (!x || !w || !y) return oc::fail(OC_ERR_ARG, "oc_conv_fwd: NULL buffer");
+  if (sh.n_out == 0) return OC_OK;
+  const size_t need = fwd_ws_bytes(t, l, sh, dt, cin, cout, parts3);
+  if (need && (!ws || ws_bytes < need))
+    return oc::fail(OC_ERR_ARG, "oc_conv_fwd: workspace %zu bytes < %zu", ws ? ws_bytes : 0, need);
+  const int relu = (flags & OC_FUSE_RELU) ? 1 : 0;
+  if (bf16_native(sh, dt, cin, cout)) {
+    oc::conv_bf16_fwd(t, l, K, (const uint16_t*)x, cin, (const uint16_t*)w, cout, y, relu, ws, s);
+    OC_LAUNCH_CHECK();
+    return OC_OK;
+  }
+  if (stride == 1) {
+    const float *x32 = (const float*)x, *w32 = (const float*)w;
+    char* rest = (char*)ws;
+    if (dt == OC_BF16) {
+      float* xw = (float*)rest;
+      float* ww = (float*)(rest + x32_bytes(sh, cin));
+      bf16_to_f32(x, sh.n_in * (int64_t)cin, xw, s);
+      bf16_to_f32(w, (int64_t)sh.K3 * cin * cout, ww, s);
+      x32 = xw, w32 = ww;
+      rest += x32_bytes(sh, cin) + w32_bytes(sh, cin, cout);
+    }
+    oc::conv_s1_fwd_f32(t, l, K, x32, cin, w32, cout, y, relu, (float*)rest, s, parts3);
+    OC_LAUNCH_CHECK();
+    return OC_OK;
+  }
+  st = oc::conv_s2_fwd(t, l, sh.r, x, cin, w, cout, dt == OC_BF16, y, relu, ws, s);
+  if (st != OC_OK) return st;
+  OC_LAUNCH_CHECK();
+  return OC_OK;
+}
+
 extern "C" {
 
 const char* oc_conv_kernel(const oc_octree* t, int32_t l, int32_t K, int32_t stride, oc_dtype dt,
@@ -223,47 +268,13 @@ const char* oc_conv_kernel(const oc_octree* t, int32_t l, int32_t K, int32_t str
 
 size_t oc_conv_fwd_workspace(const oc_octree* t, int32_t l, int32_t K, int32_t stride, oc_dtype dt,
                              int32_t cin, int32_t cout) {
-  ConvShape sh;
-  if (check_conv(t, l, K, stride, dt, cin, cout, &sh, "oc_conv_fwd_workspace") != OC_OK) return 0;
-  return fwd_ws_bytes(t, l, sh, dt, cin, cout);
+  return oc::conv_fwd_ws(t, l, K, stride, dt, cin, cout, true);
 }
 
 oc_status oc_conv_fwd(const oc_octree* t, int32_t l, int32_t K, int32_t stride, oc_dtype dt,
                       const void* x, int32_t cin, const void* w, int32_t cout, float* y,
                       void* ws, size_t ws_bytes, int32_t flags, hipStream_t s) {
-  ConvShape sh;
-  oc_status st = check_conv(t, l, K, stride, dt, cin, cout, &sh, "oc_conv_fwd");
-  if (st != OC_OK) return st;
-  if (!x || !w || !y) return oc::fail(OC_ERR_ARG, "oc_conv_fwd: NULL buffer");
-  if (sh.n_out == 0) return OC_OK;
-  const size_t need = fwd_ws_bytes(t, l, sh, dt, cin, cout);
-  if (need && (!ws || ws_bytes < need))
-    return oc::fail(OC_ERR_ARG, "oc_conv_fwd: workspace %zu bytes < %zu", ws ? ws_bytes : 0, need);
-  const int relu = (flags & OC_FUSE_RELU) ? 1 : 0;
-  if (bf16_native(sh, dt, cin, cout)) {
-    oc::conv_bf16_fwd(t, l, K, (const uint16_t*)x, cin, (const uint16_t*)w, cout, y, relu, ws, s);
-    OC_LAUNCH_CHECK();
-    return OC_OK;
-  }
-  if (stride == 1) {
-    const float *x32 = (const float*)x, *w32 = (const float*)w;
-    char* rest = (char*)ws;
-    if (dt == OC_BF16) {
-      float* xw = (float*)rest;
-      float* ww = (float*)(rest + x32_bytes(sh, cin));
-      bf16_to_f32(x, sh.n_in * (int64_t)cin, xw, s);
-      bf16_to_f32(w, (int64_t)sh.K3 * cin * cout, ww, s);
-      x32 = xw, w32 = ww;
-      rest += x32_bytes(sh, cin) + w32_bytes(sh, cin, cout);
-    }
-    oc::conv_s1_fwd_f32(t, l, K, x32, cin, w32, cout, y, relu, (float*)rest, s);
-    OC_LAUNCH_CHECK();
-    return OC_OK;
-  }
-  st = oc::conv_s2_fwd(t, l, sh.r, x, cin, w, cout, dt == OC_BF16, y, relu, ws, s);
-  if (st != OC_OK) return st;
-  OC_LAUNCH_CHECK();
-  return OC_OK;
+  return oc::conv_fwd(t, l, K, stride, dt, x, cin, w, cout, y, ws, ws_bytes, flags, true, s);
 }
 
 size_t oc_conv_pool_fwd_workspace(const oc_octree* t, int32_t l, int32_t K, oc_dtype dt,

@@ -11,15 +11,17 @@ namespace oc {
 void conv_s1_kernel_name(const oc_octree* t, int l, int K, int cin, int cout, int pass, char* buf,
                          size_t n);
 
-// Bytes of split-reduction workspace the stride-1 group-tile kernel needs for
-// kk reduction channels and nn output channels at depth l (0: none).
-size_t conv_s1_tile_ws(const oc_octree* t, int l, int K, int kk, int nn);
+// Bytes of workspace the stride-1 forward or input gradient needs for kk
+// reduction channels and nn output channels at depth l (0: none): partial
+// sums of a split reduction, or what the K = 5 kernel on three bf16 parts
+// takes.  parts3 false: that kernel is not used.
+size_t conv_s1_tile_ws(const oc_octree* t, int l, int K, int kk, int nn, bool parts3 = true);
 
 // y [N_l][cout] = conv(x [N_l][cin], w [K^3][cin][cout]), stride 1; relu != 0
-// applies max(0, .) to the output.  ws: conv_s1_tile_ws(t, l, K, cin, cout)
-// bytes.
+// applies max(0, .) to the output.  ws: conv_s1_tile_ws(t, l, K, cin, cout,
+// parts3) bytes.
 void conv_s1_fwd_f32(const oc_octree* t, int l, int K, const float* x, int cin, const float* w,
-                     int cout, float* y, int relu, float* ws, hipStream_t s);
+                     int cout, float* y, int relu, float* ws, hipStream_t s, bool parts3 = true);
 
 // True when the forward kernel of this stride-1 fp32 shape pools in its
 // epilogue (or through its split sum): conv_s1_pool_fwd_f32 then needs

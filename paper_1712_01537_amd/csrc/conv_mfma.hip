@@ -1260,10 +1260,10 @@ void launch_tile(const oc_octree* t, int l, const TileCfg& c, const float* x, in
 template <bool FLIP>
 void dispatch_tile(const oc_octree* t, int l, int K, const float* x, int kk, const float* w,
                    int nn, float* out, int relu, float* part, hipStream_t s,
-                   const RouteOut* ro = nullptr) {
+                   const RouteOut* ro = nullptr, bool parts3 = true) {
   TileCfg c = pick_tile(K, t->M[l - 1], kk, nn);
   const uint32_t* gate = nullptr;
-  if (oc::sp5_fwd_ok(t, l, K, kk, nn)) {
+  if (parts3 && oc::sp5_fwd_ok(t, l, K, kk, nn)) {
     // the launch below then works out again, in one split, what is not finite
     gate = oc::sp5_fwd(t, l, FLIP, x, kk, w, nn, out, relu, part, s);
     c.splits = 1;
@@ -1482,14 +1482,14 @@ void conv_s1_kernel_name(const oc_octree* t, int l, int K, int cin, int cout, in
            pass == 0 ? "false" : "true", c.VEC ? "true" : "false");
 }
 
-size_t conv_s1_tile_ws(const oc_octree* t, int l, int K, int kk, int nn) {
+size_t conv_s1_tile_ws(const oc_octree* t, int l, int K, int kk, int nn, bool parts3) {
   const TileCfg c = pick_tile(K, t->M[l - 1], kk, nn);
   const size_t split = c.splits > 1 ? (size_t)c.splits * t->N[l] * nn * sizeof(float) : 0;
-  return oc::sp5_fwd_ok(t, l, K, kk, nn) ? std::max(split, oc::sp5_fwd_ws(t, l, kk, nn)) : split;
+  return parts3 && sp5_fwd_ok(t, l, K, kk, nn) ? std::max(split, sp5_fwd_ws(t, l, kk, nn)) : split;
 }
 
 void conv_s1_fwd_f32(const oc_octree* t, int l, int K, const float* x, int cin, const float* w,
-                     int cout, float* y, int relu, float* ws, hipStream_t s) {
+                     int cout, float* y, int relu, float* ws, hipStream_t s, bool parts3) {
   if (conv_cin_supported(K, cin, cout)) {
     conv_cin_fwd(t, l, x, cin, w, cout, y, relu, s);
     return;
@@ -1505,7 +1505,7 @@ void conv_s1_fwd_f32(const oc_octree* t, int l, int K, const float* x, int cin, 
                       y, relu);
     return;
   }
-  dispatch_tile<false>(t, l, K, x, cin, w, cout, y, relu, ws, s);
+  dispatch_tile<false>(t, l, K, x, cin, w, cout, y, relu, ws, s, nullptr, parts3);
 }
 
 bool conv_s1_pool_fused(const oc_octree* t, int l, int K, int cin, int cout) {

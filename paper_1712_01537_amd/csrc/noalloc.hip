@@ -54,7 +54,14 @@ extern "C" oc_status oc_conv_fwd_noalloc(const oc_octree* t, int32_t l, int32_t 
   if (st != OC_OK) return st;
   if (stride != 1)  // the strided forward may call the GEMM library, which allocates
     return oc::fail(OC_ERR_UNSUPPORTED, "oc_conv_fwd_noalloc: stride %d not supported", stride);
-  const size_t need = oc_conv_fwd_workspace(t, l, K, stride, dt, cin, cout);
+  // K = 5 fp32 layers whose operands in three bf16 parts do not fit the array
+  // run on the fp32 kernel, which takes little or no workspace
+  bool parts3 = true;
+  size_t need = oc::conv_fwd_ws(t, l, K, stride, dt, cin, cout, parts3);
+  if (need > SCRATCH_BYTES) {
+    parts3 = false;
+    need = oc::conv_fwd_ws(t, l, K, stride, dt, cin, cout, parts3);
+  }
   if (need > SCRATCH_BYTES)
     return oc::fail(OC_ERR_UNSUPPORTED,
                     "oc_conv_fwd_noalloc: this call needs %zu bytes of workspace, more than the "
@@ -65,5 +72,5 @@ extern "C" oc_status oc_conv_fwd_noalloc(const oc_octree* t, int32_t l, int32_t 
     st = scratch_ptr(&p);
     if (st != OC_OK) return st;
   }
-  return oc_conv_fwd(t, l, K, stride, dt, x, cin, w, cout, y, p, need, flags, s);
+  return oc::conv_fwd(t, l, K, stride, dt, x, cin, w, cout, y, p, need, flags, parts3, s);
 }

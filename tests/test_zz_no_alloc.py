@@ -69,3 +69,30 @@ def test_noalloc_matches_workspace_forward():
     torch.cuda.synchronize()
     assert bool((y == 7.0).all())
     tree.free()
+
+
+@pytest.mark.parametrize("shapes,bits", [(4, True), (7, False)])
+def test_noalloc_k5_fp32(shapes, bits):
+    """K = 5 fp32 layers on three bf16 parts, whose workspace grows with the
+    rows: the bits of oc_conv_fwd while it fits the static array, and past it
+    the fp32 kernel, which needs none, instead of a refusal."""
+    import paper_1712_01537_amd as oc
+
+    L = oc.load()
+    pts, nrm, offs = synth.random_cloud(321, shapes, 6000, "union")
+    tree = oc.oc_build(torch.as_tensor(pts).cuda(), torch.as_tensor(nrm).cuda(), offs, 6, 2)
+    n = tree.num(6)
+    need = L.oc_conv_fwd_workspace(tree.handle, 6, 5, 1, 0, 64, 64)
+    print(f"[noalloc] K5 f32 64->64 rows {n} workspace {need} bytes", flush=True)
+    assert need >= 6 * 64 * n and (need <= 32 << 20) == bits
+    g = torch.Generator("cuda").manual_seed(321)
+    x = torch.randn((n, 64), generator=g, device="cuda")
+    w = torch.randn((125, 64, 64), generator=g, device="cuda") / 8000 ** 0.5
+    ref = oc.oc_conv_fwd(tree, 6, 5, 1, x, w)
+    y = torch.full((n, 64), float("nan"), device="cuda")
+    assert _raw_noalloc(L, tree, 6, 5, x, w, y, False) == 0, L.oc_last_error()
+    if bits:
+        assert torch.equal(y.view(torch.int32), ref.view(torch.int32))
+    else:  # 8000 products in sequence: as many roundings of either sign, and the other's
+        assert float((y - ref).norm()) <= 2 * 8000 ** 0.5 * 2.0 ** -24 * float(ref.norm())
+    tree.free()
