@@ -41,6 +41,14 @@ FLAGS = [
 COUNTED_WAIT = re.compile(r"s_waitcnt vmcnt\(%")
 
 
+# Kernels that keep their weights and sums in registers for a whole launch: an
+# array that ends in scratch memory instead (a lambda that is not inlined, a
+# loop that is not unrolled) was measured to cost k_conv_sp3 a factor of 2.5.
+# Their variants for inputs of 4 GiB and more (last template argument true)
+# hold 64-bit addresses beside these and may spill.
+IN_REGISTERS = re.compile(r"k_conv_(?:sp3|dws)I(?:L[ib]\d+E)*Lb0EE+v")
+
+
 def _scratch_by_kernel(remarks: str) -> dict:
     """Kernel (mangled name) -> scratch bytes per lane, from the compiler's
     -Rpass-analysis=kernel-resource-usage remarks."""
@@ -56,6 +64,18 @@ def _scratch_by_kernel(remarks: str) -> dict:
     return out
 
 
+def scratch_fault(text: str, remarks: str) -> str:
+    """What is wrong with the scratch memory of a source's kernels; "" for nothing."""
+    used = {k: v for k, v in _scratch_by_kernel(remarks).items() if v > 0}
+    if used and COUNTED_WAIT.search(text):
+        return ("holds counted vmcnt waits, but these kernels use scratch memory (bytes/lane), "
+                f"which breaks the counts: {used}")
+    slow = {k: v for k, v in used.items() if IN_REGISTERS.search(k)}
+    if slow:
+        return f"these kernels' arrays have to stay in registers (scratch bytes/lane): {slow}"
+    return ""
+
+
 def _compile(src: str) -> str:
     obj = os.path.join(OBJ, os.path.basename(src) + ".o")
     cmd = [HIPCC, *FLAGS, "-Rpass-analysis=kernel-resource-usage", "-c", src, "-o", obj]
@@ -63,13 +83,10 @@ def _compile(src: str) -> str:
     if r.returncode != 0:
         raise RuntimeError(f"hipcc failed for {src}:\n{r.stdout}\n{r.stderr}")
     with open(src) as fh:
-        counted = COUNTED_WAIT.search(fh.read()) is not None
-    if counted:
-        bad = {k: v for k, v in _scratch_by_kernel(r.stderr).items() if v > 0}
-        if bad:
-            os.remove(obj)
-            raise RuntimeError(f"{src} holds counted vmcnt waits, but these kernels use scratch "
-                               f"memory (bytes/lane), which breaks the counts: {bad}")
+        why = scratch_fault(fh.read(), r.stderr)
+    if why:
+        os.remove(obj)
+        raise RuntimeError(f"{src}: {why}")
     return obj
 
 

@@ -88,6 +88,10 @@ __device__ __forceinline__ v4u tr2(const char* p, int next) {
 // block 0 zero an equal share of the rows of empty depth-(l-1) octants
 // (plab[i] == 0).
 // BIG: x is 4 GiB or more, too large for 32-bit offsets.
+// Every lambda of the tile loop is inlined by force: one that is not, as the
+// compiler decided for <4, 8, false, true, false>, takes wr, acc and prq by
+// address and so puts them in scratch memory (16 -> 64 pooled, 69765 groups: 492
+// us instead of 190).
 //
 // Measured on an MI355X (main kernel alone, 32 shapes at depth 6; before: the
 // fp32 MFMA kernel this one replaced, 16x16x4, weights in registers): 16->64
@@ -250,7 +254,7 @@ __global__ __launch_bounds__(TB) __attribute__((amdgpu_waves_per_eu(2))) void k_
   // of P row blocks, whose products are taken in turn, so that one need not
   // wait for the one before it (with one block, two sums do that); the reads
   // of the D-th next unit are issued before a unit's MFMAs.
-  auto compute = [&](const v4u* buf, int rb0, auto half, auto nbt, v4f* acc) {
+  auto compute = [&](const v4u* buf, int rb0, auto half, auto nbt, v4f* acc) __attribute__((always_inline)) {
     constexpr int NB = decltype(nbt)::value, S0 = decltype(half)::value * (NST / 2);
     constexpr int P = NB >= 2 ? 2 : 1, U = NST / 2 * NB / P, D = P == 1 ? 2 : 1;
     const v4u* bb = buf + 2 * rb0 * GS;
@@ -296,7 +300,7 @@ __global__ __launch_bounds__(TB) __attribute__((amdgpu_waves_per_eu(2))) void k_
   float* dst = split ? part + (int64_t)blockIdx.z * nrows * nn : out;
   // What is not finite is worked out in plain fp32: lane l's four values are
   // output channels n0 + 4 q .. + 3 of row li of row block rb.
-  auto mend = [&](int64_t g, v4f& v) {
+  auto mend = [&](int64_t g, v4f& v) __attribute__((always_inline)) {
     if (g >= g1) return;
     const int c = li & 7, ce = std::min(kk, c0 + 16);
     for (int j = 0; j < 4; ++j) {
@@ -316,7 +320,7 @@ __global__ __launch_bounds__(TB) __attribute__((amdgpu_waves_per_eu(2))) void k_
     }
   };
   // row block rb of the tile that starts at group gt
-  auto store_rb = [&](int64_t gt, int rb, v4f v, int32_t pr) {
+  auto store_rb = [&](int64_t gt, int rb, v4f v, int32_t pr) __attribute__((always_inline)) {
     if constexpr (POOL) {
       // through the wave's LDS area: lane o < 32 pools group o/16 of the
       // row block in channel n0 + o%16
@@ -351,7 +355,7 @@ __global__ __launch_bounds__(TB) __attribute__((amdgpu_waves_per_eu(2))) void k_
   v4f acc[RB];
   int32_t prq[RB];
   // the wave's row blocks of tile t, the first at group g0 + t GPB + 2 wm RB
-  auto multiply = [&](int t, auto half) {
+  auto multiply = [&](int t, auto half) __attribute__((always_inline)) {
     const v4u* buf = X + (t & 1) * BUFC;
     const int64_t left = g1 - g0 - (int64_t)t * GPB - 2 * wm * RB;  // groups from there on
     if (left > 2 * (RB - 1)) {
@@ -364,7 +368,7 @@ __global__ __launch_bounds__(TB) __attribute__((amdgpu_waves_per_eu(2))) void k_
       }
     }
   };
-  auto finish = [&](int t) {  // first half: write tile t
+  auto finish = [&](int t) __attribute__((always_inline)) {  // first half: write tile t
     const v4f* ex = &EX[t & 1][wv][lane];
     const int64_t gt = g0 + (int64_t)t * GPB;
     v4f v[RB];
@@ -389,7 +393,7 @@ __global__ __launch_bounds__(TB) __attribute__((amdgpu_waves_per_eu(2))) void k_
       load_nb(t + 4);
     }
   };
-  auto phase = [&](int t, v4f (&rx)[NU]) {
+  auto phase = [&](int t, v4f (&rx)[NU]) __attribute__((always_inline)) {
     lds_barrier();
     if (th == 0) {
       if (t > 0) finish(t - 1);

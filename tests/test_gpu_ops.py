@@ -193,6 +193,35 @@ def test_conv_split_4gib():
     assert torch.equal(y, ys)
 
 
+def _median_us(f, n=15):
+    for _ in range(3):
+        f()
+    t = []
+    for _ in range(n):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        f()
+        b.record()
+        torch.cuda.synchronize()
+        t.append(a.elapsed_time(b) * 1e3)
+    return sorted(t)[n // 2]
+
+
+@pytest.mark.parametrize("cout", [32, 64])
+def test_conv_pool_cost(cout):
+    """The pooled forward of a layer with one 16-channel chunk costs about what the
+    plain forward does (with its tile's arrays in scratch memory, three times)."""
+    oc = _oc()
+    pts, nrm, offs = synth.random_cloud(221, 32, 6000, "union")
+    tree = oc.oc_build(torch.as_tensor(pts).cuda(), torch.as_tensor(nrm).cuda(), offs, 6, 2)
+    x = torch.randn((tree.num(6), 16), device="cuda")
+    w = torch.randn((27, 16, cout), device="cuda")
+    plain = _median_us(lambda: oc.oc_conv_fwd(tree, 6, 3, 1, x, w))
+    pooled = _median_us(lambda: oc.oc_conv_pool_fwd(tree, 6, 3, x, w))
+    print(f"[cost] 16->{cout} {tree.num(6)} rows: plain {plain:.0f} us, pooled {pooled:.0f}")
+    assert pooled <= 2 * plain
+
+
 SPLIT_K5 = [  # seed, B, n, depth, cin, cout, which passes run on three bf16 parts
     (301, 7, 6000, 6, 64, 64, (1, 1, 1)),    # one block of channels and columns
     (302, 7, 6003, 6, 32, 64, (1, 0, 0)),    # three chunks of two products each
