@@ -298,26 +298,58 @@ __global__ __launch_bounds__(TB) __attribute__((amdgpu_waves_per_eu(2))) void k_
   const int64_t nrows = 8 * ngroups;
   const bool split = gridDim.z > 1;
   float* dst = split ? part + (int64_t)blockIdx.z * nrows * nn : out;
-  // What is not finite is worked out in plain fp32: lane l's four values are
-  // output channels n0 + 4 q .. + 3 of row li of row block rb.
+  // What is not finite is worked out again with fp32 MFMAs (16x16x4), by the
+  // whole wave: lane l's four values are output channels n0 + 4 q .. + 3 of row
+  // li of a row block, a row of group g.  Step j of a tap takes the channels
+  // c0 + 4 q + j, so that a lane's four are one load of x.  The loads of three
+  // taps are in flight together; absent neighbours read as zeros.
+  // All NaN, 24 -> 40 channels on 12924 groups: 350 us (67 with ordinary values;
+  // 106 in the fp32 kernel that this one replaced; 10600 with a serial sum per
+  // value); 16 -> 16 on 9205: 41 (14; 21; 1030).
   auto mend = [&](int64_t g, v4f& v) __attribute__((always_inline)) {
-    if (g >= g1) return;
-    const int c = li & 7, ce = std::min(kk, c0 + 16);
-    for (int j = 0; j < 4; ++j) {
-      const int n = n0 + 4 * q + j;
-      if (n >= nn || fabsf(v[j]) < __builtin_inff()) continue;
-      float s = 0.f;
-      for (int k = 0; k < 27; ++k) {
-        const int vx = (c >> 2) + k / 9 - 1, vy = ((c >> 1) & 1) + k / 3 % 3 - 1,
-                  vz = (c & 1) + k % 3 - 1;
-        const int32_t nb = nbr[27 * g + ((vx >> 1) + 1) * 9 + ((vy >> 1) + 1) * 3 + (vz >> 1) + 1];
-        const int64_t row = (int64_t)(nb + 4 * (vx & 1) + 2 * (vy & 1) + (vz & 1)) * kk;
-        for (int ch = c0; ch < ce; ++ch)  // absent neighbours read as zero
-          s = fmaf(nb < 0 ? 0.f : x[row + ch], FLIP ? w[((int64_t)(26 - k) * nn + n) * kk + ch]
-                                                    : w[((int64_t)k * kk + ch) * nn + n], s);
+    int ln = lane;
+    asm volatile("" : "+v"(ln));  // nothing of this is worked out ahead of the tile loop
+    const int c = ln & 7, ch = c0 + 4 * (ln >> 4), n = n0 + (ln & 15);
+    const int32_t* nb = nbr + 27 * (g < g1 ? g : g0);
+    const __amdgpu_buffer_rsrc_t rw = rsrc(w, (uint32_t)(27 * kk * nn * 4));
+    const uint32_t ow = n >= nn || ch >= kk ? ~0u : FLIP ? 4 * (n * kk + ch) : 4 * (ch * nn + n);
+    v4f s = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+    for (int kxy = 0; kxy < 9; ++kxy) {
+      const int vx = (c >> 2) + kxy / 3 - 1, vy = ((c >> 1) & 1) + kxy % 3 - 1;
+      v4f a[3], b[3];
+#pragma unroll
+      for (int kz = 0; kz < 3; ++kz) {
+        const int vz = (c & 1) + kz - 1, k = 3 * kxy + kz;
+        const int32_t e = nb[((vx >> 1) + 1) * 9 + ((vy >> 1) + 1) * 3 + (vz >> 1) + 1];
+        const int64_t row = e + 4 * (vx & 1) + 2 * (vy & 1) + (vz & 1);
+        if constexpr (BIG) {
+          b[kz] = v4f{0.f, 0.f, 0.f, 0.f};
+          if (e >= 0 && ch < kk) b[kz] = *reinterpret_cast<const v4f*>(x + row * kk + ch);
+        } else {
+          const uint32_t off = (uint32_t)row * (uint32_t)(4 * kk) + 4 * ch;
+          b[kz] = __builtin_bit_cast(
+              v4f, __builtin_amdgcn_raw_buffer_load_b128(rx_, e < 0 || ch >= kk ? ~0u : off, 0, 0));
+        }
+        if constexpr (FLIP) {
+          a[kz] = __builtin_bit_cast(
+              v4f, __builtin_amdgcn_raw_buffer_load_b128(rw, ow, 4 * (26 - k) * nn * kk, 0));
+        } else {
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            a[kz][j] = __builtin_bit_cast(
+                float, __builtin_amdgcn_raw_buffer_load_b32(rw, ow, 4 * (k * kk + j) * nn, 0));
+        }
       }
-      v[j] = s;
+#pragma unroll
+      for (int kz = 0; kz < 3; ++kz)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          s = __builtin_amdgcn_mfma_f32_16x16x4f32(a[kz][j], b[kz][j], s, 0, 0, 0);
     }
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (!(fabsf(v[j]) < __builtin_inff())) v[j] = s[j];
   };
   // row block rb of the tile that starts at group gt
   auto store_rb = [&](int64_t gt, int rb, v4f v, int32_t pr) __attribute__((always_inline)) {
@@ -380,7 +412,8 @@ __global__ __launch_bounds__(TB) __attribute__((amdgpu_waves_per_eu(2))) void k_
     }
     if (__builtin_expect(__any(bad), 0)) {
 #pragma unroll
-      for (int r = 0; r < RB; ++r) mend(gt + 2 * (wm * RB + r) + (li >> 3), v[r]);
+      for (int r = 0; r < RB; ++r)
+        if (__any(oc::s3_bad(v[r]))) mend(gt + 2 * (wm * RB + r) + (li >> 3), v[r]);
     }
 #pragma unroll
     for (int r = 0; r < RB; ++r) store_rb(gt, wm * RB + r, v[r], POOL ? prq[r] : 0);
@@ -477,7 +510,9 @@ void launch_sp3(const oc_octree* t, int l, int splits, const float* x, int kk, c
 // group are then distinct mod 8, which is all 64 banks.  dY: part, group, child
 // rows of 32 NBN bytes, groups padded to the same end.
 //
-// What is not finite is worked out again, wave by wave, with fp32 MFMAs.
+// What is not finite is worked out again, wave by wave, with fp32 MFMAs: 243 us
+// for all NaN, 24 -> 40 channels on 12924 groups (85 with ordinary values, 112 in
+// the kernel before).
 //
 // Measured on an MI355X (before: an fp32 16x16x4 kernel of the same tiles):
 // 16 -> 16 channels on 218768 groups 174 us, 139 TFLOP/s of fp32 products; the
@@ -685,31 +720,49 @@ __global__ __launch_bounds__(TB) __attribute__((amdgpu_waves_per_eu(2))) void k_
     for (int j = 0; j < NJ; ++j)
 #pragma unroll
       for (int n = 0; n < NBN; ++n) acc[j][n] = v4f{0.f, 0.f, 0.f, 0.f};
-    for (int s = 0; s < nsub; ++s)
-      for (int i = 0; i < 2 * GS; ++i) {
-        const int gl = first(s) + (i >> 1);
-        if (gl >= ng) break;
-        const int64_t g = gb + gl;
-        const int c = 4 * (i & 1) + q;  // the lane group's child
-        float bv[NBN];
+    for (int i = 0; i < nsub * GS; ++i) {  // a sibling group: its eight children in two steps
+      const int gl = first(i / GS) + i % GS;
+      if (gl >= ng) break;
+      int32_t e[2][NJ];
+      float av[2][NJ], bv[2][NBN];
 #pragma unroll
-        for (int n = 0; n < NBN; ++n) {
-          const int col = n0 + 16 * n + li;
-          bv[n] = col < cout ? dy[(8 * g + c) * cout + col] : 0.f;
-        }
+      for (int h = 0; h < 2; ++h)  // child 4 h + q: the lane group's
 #pragma unroll
         for (int j = 0; j < NJ; ++j) {
           const int tap = wave + 4 * j < 27 ? wave + 4 * j : 0;
-          const int vx = (c >> 2) + tap / 9 - 1, vy = ((c >> 1) & 1) + tap / 3 % 3 - 1,
-                    vz = (c & 1) + tap % 3 - 1;
-          const int32_t e = nbr[27 * g + ((vx >> 1) + 1) * 9 + ((vy >> 1) + 1) * 3 + (vz >> 1) + 1];
-          const int64_t row = (int64_t)e + 4 * (vx & 1) + 2 * (vy & 1) + (vz & 1);
-          const float av = e >= 0 && c0 + li < cin ? x[row * cin + c0 + li] : 0.f;
+          const int vx = h + tap / 9 - 1, vy = (q >> 1) + tap / 3 % 3 - 1, vz = (q & 1) + tap % 3 - 1;
+          const int sl = ((vx >> 1) + 1) * 9 + ((vy >> 1) + 1) * 3 + (vz >> 1) + 1;
+          const int32_t v = __builtin_amdgcn_raw_buffer_load_b32(rn, 4 * sl, 108 * gl, 0);
+          e[h][j] = v < 0 ? v : v + 4 * (vx & 1) + 2 * (vy & 1) + (vz & 1);
+        }
 #pragma unroll
-          for (int n = 0; n < NBN; ++n)
-            acc[j][n] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, bv[n], acc[j][n], 0, 0, 0);
+      for (int h = 0; h < 2; ++h) {
+#pragma unroll
+        for (int n = 0; n < NBN; ++n) {
+          const int col = n0 + 16 * n + li;
+          bv[h][n] = col < cout ? dy[(8 * (gb + gl) + 4 * h + q) * cout + col] : 0.f;
+        }
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+          const bool live = e[h][j] >= 0 && c0 + li < cin;
+          if constexpr (BIG) {
+            av[h][j] = live ? x[(int64_t)e[h][j] * cin + c0 + li] : 0.f;
+          } else {
+            const uint32_t off = (uint32_t)e[h][j] * (uint32_t)(4 * cin) + 4 * (c0 + li);
+            av[h][j] = __builtin_bit_cast(
+                float, __builtin_amdgcn_raw_buffer_load_b32(rx_, live ? off : ~0u, 0, 0));
+          }
         }
       }
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+#pragma unroll
+          for (int n = 0; n < NBN; ++n)
+            acc[j][n] =
+                __builtin_amdgcn_mfma_f32_16x16x4f32(av[h][j], bv[h][n], acc[j][n], 0, 0, 0);
+    }
   } else if (half) {
 #pragma unroll
     for (int j = 0; j < NJ; ++j)

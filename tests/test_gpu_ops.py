@@ -222,6 +222,26 @@ def test_conv_pool_cost(cout):
     assert pooled <= 2 * plain
 
 
+@pytest.mark.parametrize("cin,cout", [(16, 16), (24, 40)])
+def test_conv_split_not_finite_cost(cin, cout):
+    """A diverged layer, all NaN, is formed again in plain fp32 by whole waves: a
+    few times an ordinary layer's time (a serial sum per value: over 70 times)."""
+    oc = _oc()
+    pts, nrm, offs = synth.random_cloud(222, 5, 6000, "union")
+    tree = oc.oc_build(torch.as_tensor(pts).cuda(), torch.as_tensor(nrm).cuda(), offs, 6, 2)
+    n = tree.num(6)
+    w = torch.randn((27, cin, cout), device="cuda")
+    x, dy = torch.randn((n, cin), device="cuda"), torch.randn((n, cout), device="cuda")
+    calls = (lambda x, dy: oc.oc_conv_fwd(tree, 6, 3, 1, x, w),
+             lambda x, dy: oc.oc_conv_pool_fwd(tree, 6, 3, x, w),
+             lambda x, dy: oc.oc_conv_bwd(tree, 6, 3, 1, x, w, dy, need_dw=False),
+             lambda x, dy: oc.oc_conv_bwd(tree, 6, 3, 1, x, w, dy, need_dx=False))
+    for i, call in enumerate(calls):
+        us = [_median_us(lambda: call(x * f, dy * f)) for f in (1.0, float("nan"))]
+        print(f"[cost] {cin}->{cout} call {i}: {us[0]:.0f} us, all NaN {us[1]:.0f}", flush=True)
+        assert us[1] <= 12 * us[0]
+
+
 SPLIT_K5 = [  # seed, B, n, depth, cin, cout, which passes run on three bf16 parts
     (301, 7, 6000, 6, 64, 64, (1, 1, 1)),    # one block of channels and columns
     (302, 7, 6003, 6, 32, 64, (1, 0, 0)),    # three chunks of two products each
