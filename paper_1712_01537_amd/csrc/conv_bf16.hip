@@ -884,7 +884,10 @@ __global__ __launch_bounds__(NW_ * 64, 8 / NW_) void k_conv_bfw(const int32_t* _
     if (row < nrows && n < nn) {
       v4fu* dst = reinterpret_cast<v4fu*>(out + row * nn + n);
       if (acc_in) sum = (v4f)*dst + sum;
-      if (SP && oc::s3_bad(sum)) *bad = 1;
+      if constexpr (SP) {
+        sum *= oc::kSplitDown;
+        if (oc::s3_bad(sum)) *bad = 1;
+      }
       if (relu) {
 #pragma unroll
         for (int j = 0; j < 4; ++j) sum[j] = fmaxf(sum[j], 0.f);
@@ -1200,10 +1203,13 @@ __global__ __launch_bounds__(NW * 64, 8 / NW) void k_conv_bf_dw(const int32_t* _
       for (int nb = 0; nb < 4; ++nb) {
         const int n = n0 + 16 * nb + li;
         if (n < cout) {
-          if (SP && oc::s3_bad(acc[mi][nb])) *bad = 1;
+          v4f v = acc[mi][nb];
+          if constexpr (SP) {
+            v *= oc::kSplitDown;
+            if (oc::s3_bad(v)) *bad = 1;
+          }
 #pragma unroll
-          for (int j = 0; j < 4; ++j)
-            dst[(int64_t)(c0 + 16 * cb + 4 * q + j) * cout + n] = acc[mi][nb][j];
+          for (int j = 0; j < 4; ++j) dst[(int64_t)(c0 + 16 * cb + 4 * q + j) * cout + n] = v[j];
         }
       }
     }

@@ -407,7 +407,7 @@ __global__ __launch_bounds__(TB) __attribute__((amdgpu_waves_per_eu(2))) void k_
     bool bad = false;
 #pragma unroll
     for (int r = 0; r < RB; ++r) {
-      v[r] = acc[r] + ex[64 * r];
+      v[r] = (acc[r] + ex[64 * r]) * oc::kSplitDown;
       bad |= oc::s3_bad(v[r]);
     }
     if (__builtin_expect(__any(bad), 0)) {
@@ -610,7 +610,7 @@ __global__ __launch_bounds__(TB) __attribute__((amdgpu_waves_per_eu(2))) void k_
     }
     if (yon) {
       v2u p[3];
-      oc::s3_split4(sk, half ? -ry : ry, p);
+      oc::s3_split4(sk, ry, p, half ? -oc::kSplitUp : oc::kSplitUp);
 #pragma unroll
       for (int k = 0; k < 3; ++k) *reinterpret_cast<v2u*>(b + ly + k * YP) = p[k];
     }
@@ -763,11 +763,12 @@ __global__ __launch_bounds__(TB) __attribute__((amdgpu_waves_per_eu(2))) void k_
             acc[j][n] =
                 __builtin_amdgcn_mfma_f32_16x16x4f32(av[h][j], bv[h][n], acc[j][n], 0, 0, 0);
     }
-  } else if (half) {
+  } else {
+    const float down = half ? -oc::kSplitDown : oc::kSplitDown;
 #pragma unroll
     for (int j = 0; j < NJ; ++j)
 #pragma unroll
-      for (int n = 0; n < NBN; ++n) acc[j][n] = -acc[j][n];
+      for (int n = 0; n < NBN; ++n) acc[j][n] *= down;
   }
 
   // halves add their sums: tap j goes to half j < JH ? 0 : 1

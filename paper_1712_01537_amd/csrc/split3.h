@@ -2,7 +2,12 @@
 //
 // An fp32 value is the sum of three bf16 values: hi = x rounded to bf16, mid =
 // (x - hi) rounded to bf16, lo = x - hi - mid (both differences are exact, and
-// 3 x 8 significand bits hold the 24 of an fp32 value, so lo is exact too).  A
+// 3 x 8 significand bits hold the 24 of an fp32 value, so lo is exact too,
+// unless it is too small for a bf16 value).  Values are therefore multiplied by
+// 2^24 before they are split: a part is then a multiple of 2^-125, since an
+// fp32 value is one of 2^-149, and none is subnormal.  Sums of products are
+// multiplied by 2^-48 at the end; both factors are exact.  Without them a
+// value of 2^-120 keeps 14 of its bits.  A
 // product x w is then the sum of nine bf16 products, each exact in fp32.  Six
 // are kept: lo hi', hi lo', mid mid', mid hi', hi mid', hi hi'.  Rounding to
 // nearest bounds mid by 2^-8 |x| and lo by 2^-17 |x|, so the three left out
@@ -12,9 +17,9 @@
 // A bf16 MFMA (16x16x32, 16 cycles) has 16 times the rate of the fp32 one
 // (16x16x4, 32 cycles), so six of them do the same work in 3/8 of the time.
 //
-// Values whose bf16 rounding is infinite (above 3.39e38), infinities and NaN
-// have no such sum: a kernel that uses it checks its accumulators and works
-// out what is not finite once more in plain fp32.
+// Values of 2^103 (1e31) and more, infinities and NaN have no such sum, and
+// results of 2^80 (1.2e24) and more overflow: a kernel that uses it checks its
+// accumulators and works out what is not finite once more in plain fp32.
 #pragma once
 
 #include "common.h"
@@ -50,7 +55,10 @@ __device__ __forceinline__ SplitK s3_consts() {
   return SplitK{__builtin_bit_cast(s3_v2bf, a), __builtin_bit_cast(s3_v2bf, b)};
 }
 
-// Parts of two values, packed as s3_round2 does.  A difference is one dot
+constexpr float kSplitUp = 0x1p24f;     // factor of a value before it is split
+constexpr float kSplitDown = 0x1p-48f;  // factor of a sum of products
+
+// Parts of two scaled values, packed as s3_round2 does.  A difference is one dot
 // product of the rounded pair with (-1, 0) or (0, -1), added to the value; it
 // equals the fp32 subtraction bit for bit (subnormal results included).
 __device__ __forceinline__ void s3_split2(const SplitK& k, float a, float b, uint32_t& h,
@@ -66,12 +74,13 @@ __device__ __forceinline__ void s3_split2(const SplitK& k, float a, float b, uin
   l = s3_round2(a, b);
 }
 
-// Four values' parts.
-__device__ __forceinline__ void s3_split4(const SplitK& k, const s3_v4f& v, s3_v2u (&p)[3]) {
+// Four values' parts, scaled by up (kSplitUp or -kSplitUp).
+__device__ __forceinline__ void s3_split4(const SplitK& k, const s3_v4f& v, s3_v2u (&p)[3],
+                                          float up = kSplitUp) {
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
     uint32_t h, m, l;
-    s3_split2(k, v[2 * i], v[2 * i + 1], h, m, l);
+    s3_split2(k, v[2 * i] * up, v[2 * i + 1] * up, h, m, l);
     p[0][i] = h, p[1][i] = m, p[2][i] = l;
   }
 }
@@ -82,7 +91,7 @@ __device__ __forceinline__ Split8 s3_split8(const SplitK& k, const s3_v4f& a, co
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     uint32_t h, m, l;
-    s3_split2(k, v[2 * i], v[2 * i + 1], h, m, l);
+    s3_split2(k, v[2 * i] * kSplitUp, v[2 * i + 1] * kSplitUp, h, m, l);
     r.p[0][i] = h, r.p[1][i] = m, r.p[2][i] = l;
   }
   return r;
@@ -93,7 +102,7 @@ __device__ __forceinline__ s3_v4f s3_mfma(const s3_v4u& a, const s3_v4u& b, cons
                                                  __builtin_bit_cast(s3_v8bf, b), c, 0, 0, 0);
 }
 
-// Product i = 0..5 of a and b added to c, the smallest first.
+// Product i = 0..5 of a and b added to c (in units of 2^-48), the smallest first.
 __device__ __forceinline__ s3_v4f s3_product(int i, const s3_v4u (&a)[3], const s3_v4u (&b)[3],
                                              const s3_v4f& c) {
   constexpr int ia[6] = {2, 0, 1, 1, 0, 0}, ib[6] = {0, 2, 1, 0, 1, 0};

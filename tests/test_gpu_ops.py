@@ -193,6 +193,49 @@ def test_conv_split_4gib():
     assert torch.equal(y, ys)
 
 
+@pytest.mark.parametrize("K,cin,cout", [(3, 16, 16), (3, 20, 64), (5, 64, 64)])
+@pytest.mark.parametrize("a,b", [(-120, 95), (95, -120), (-135, 100), (-145, 120), (-100, -40)])
+def test_conv_split_small_operands(K, cin, cout, a, b):
+    """One operand of every product about 2^a, the other about 2^b: the three bf16
+    parts hold all bits of each, subnormal ones too.  (-145, 120): above 2^103,
+    where plain fp32 takes over.  (-100, -40): the results are subnormal, below
+    2^-126 where an fp32 sum has steps of 2^-149 for each of its terms."""
+    oc = _oc()
+    ref, tree = _trees(*synth.random_cloud(231, 7 if K == 5 else 2, 6000 if K == 5 else 500, "union"),
+                       6 if K == 5 else 4)
+    l = tree.depth
+    N, K3 = ref.num(l), K ** 3
+    nb = torch.as_tensor(np.asarray(ref.neighbors(l, K))).long()
+    nb = torch.where(nb < 0, N, nb).cuda()
+    g = torch.Generator("cuda").manual_seed(K * 1000 + cin)
+
+    def draw(e, *shape):  # fp32 values about 2^e (rounded to 2^-149, as subnormals are)
+        return (torch.randn(shape, generator=g, device="cuda").double() * 2.0 ** e).float()
+
+    def pad(v):
+        return torch.cat([v, v.new_zeros((1, v.shape[1]))]).double()
+
+    def check(tag, got, want, terms):
+        err = torch.linalg.norm(got.double() - want)
+        steps = math.sqrt(terms * want.numel()) * 2.0 ** -149
+        # sums of a few thousand terms in plain fp32 have up to sqrt(terms) 2^-24
+        tol = 1e-6 if max(a, b) < 103 else math.sqrt(terms) * 2.0 ** -24
+        assert err <= tol * torch.linalg.norm(want) + steps, (tag, float(err / torch.linalg.norm(want)))
+
+    x, w = draw(a, N, cin), draw(b, K3, cin, cout)
+    xp = pad(x)
+    y = sum(xp[nb[:, k]] @ w[k].double() for k in range(K3))
+    check("y", oc.oc_conv_fwd(tree, l, K, 1, x, w), y, K3 * cin)
+    dy = draw(a, N, cout)
+    dp = pad(dy)
+    dx, _ = oc.oc_conv_bwd(tree, l, K, 1, x, w, dy, need_dw=False)
+    check("dx", dx, sum(dp[nb[:, K3 - 1 - k]] @ w[k].double().t().contiguous() for k in range(K3)),
+          K3 * cout)
+    dy = draw(b, N, cout)
+    _, dw = oc.oc_conv_bwd(tree, l, K, 1, x, w, dy, need_dx=False)
+    check("dw", dw, torch.stack([xp[nb[:, k]].t().contiguous() @ dy.double() for k in range(K3)]), N)
+
+
 def _median_us(f, n=15):
     for _ in range(3):
         f()
