@@ -1471,7 +1471,7 @@ void conv_s1_kernel_name(const oc_octree* t, int l, int K, int cin, int cout, in
   const int kk = pass == 0 ? cin : cout, nn = pass == 0 ? cout : cin;
   const TileCfg c = pick_tile(K, t->M[l - 1], kk, nn);
   if (c.v2) {
-    oc::sp3_name(oc::sp3_pick(t->M[l - 1], kk, nn), pass == 1, pooled, buf, n);
+    oc::sp3_name(t, l, oc::sp3_pick(t->M[l - 1], kk, nn), pass == 1, pooled, kk, buf, n);
     return;
   }
   if (sp5_fwd_ok(t, l, K, kk, nn)) {

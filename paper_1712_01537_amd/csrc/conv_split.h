@@ -30,7 +30,8 @@ void sp3_launch(const oc_octree* t, int l, const Sp3Cfg& cfg, bool flip, const f
                 hipStream_t s);
 
 // Kernel name with template arguments.
-void sp3_name(const Sp3Cfg& cfg, bool flip, bool pooled, char* buf, size_t n);
+void sp3_name(const oc_octree* t, int l, const Sp3Cfg& cfg, bool flip, bool pooled, int kk, char* buf,
+              size_t n);
 
 // Partial sums part[nchunks][27][cin][cout] of the K = 3 weight gradient over
 // chunks of gchunk sibling groups (cin >= 16, cin and cout multiples of 4),

@@ -16,6 +16,11 @@ typedef oc::s3_v4u v4u;
 constexpr int TB = 512;
 constexpr int WAVES = TB / 64;
 
+// Rows of c channels at depth l too large for 32-bit byte offsets (BIG below).
+bool rows_big(const oc_octree* t, int l, int c) {
+  return t->N[l] * c * 4 >= int64_t(1) << 32;
+}
+
 // A 16x16 MFMA result held as D[4(l/16)+j][l%16] in lane l (j = 0..3) is
 // handed over so that lane l holds D[4(l%4)+j][l/4]: with rows l%16 of the
 // result as output rows, consecutive lanes then store consecutive 16 bytes.
@@ -480,7 +485,7 @@ void launch_sp3b(const oc_octree* t, int l, int splits, const float* x, int kk, 
 template <int WN, int GPB, bool FLIP, bool POOL>
 void launch_sp3(const oc_octree* t, int l, int splits, const float* x, int kk, const float* w,
                 int nn, float* out, int relu, float* part, const oc::Sp3Pool* po, hipStream_t s) {
-  if (t->N[l] * kk * 4 >= int64_t(1) << 32)
+  if (rows_big(t, l, kk))
     launch_sp3b<WN, GPB, FLIP, POOL, true>(t, l, splits, x, kk, w, nn, out, relu, part, po, s);
   else
     launch_sp3b<WN, GPB, FLIP, POOL, false>(t, l, splits, x, kk, w, nn, out, relu, part, po, s);
@@ -802,7 +807,7 @@ __global__ __launch_bounds__(TB) __attribute__((amdgpu_waves_per_eu(2))) void k_
 template <int NBN>
 void launch_dws(const oc_octree* t, int l, int64_t gchunk, int64_t nchunks, const float* x,
                 int cin, const float* dy, int cout, float* part, hipStream_t s) {
-  const bool big = t->N[l] * std::max(cin, cout) * 4 >= int64_t(1) << 32;
+  const bool big = rows_big(t, l, std::max(cin, cout));
   const auto kernel = big ? k_conv_dws<NBN, true> : k_conv_dws<NBN, false>;
   const dim3 grid((unsigned)nchunks, (unsigned)(oc::cdiv(cin, 16) * oc::cdiv(cout, 16 * NBN)));
   oc::launch_main(kernel, grid, dim3(TB), s, (const int32_t*)t->nbr[l], t->M[l - 1], gchunk, x, cin,
@@ -853,9 +858,11 @@ void sp3_launch(const oc_octree* t, int l, const Sp3Cfg& c, bool flip, const flo
 #undef OC_SP3
 }
 
-void sp3_name(const Sp3Cfg& c, bool flip, bool pooled, char* buf, size_t n) {
-  snprintf(buf, n, "k_conv_sp3<%d, %d, %s, %s>", c.wn, c.gpb, flip ? "true" : "false",
-           pooled && c.splits == 1 ? "true" : "false");
+void sp3_name(const oc_octree* t, int l, const Sp3Cfg& c, bool flip, bool pooled, int kk, char* buf,
+              size_t n) {
+  const char* const tf[2] = {"false", "true"};
+  snprintf(buf, n, "k_conv_sp3<%d, %d, %s, %s, %s>", c.wn, c.gpb, tf[flip],
+           tf[pooled && c.splits == 1], tf[rows_big(t, l, kk)]);
 }
 
 void dws_launch(const oc_octree* t, int l, int nbn, int64_t gchunk, int64_t nchunks, const float* x,
@@ -867,8 +874,7 @@ void dws_launch(const oc_octree* t, int l, int nbn, int64_t gchunk, int64_t nchu
 }
 
 void dws_name(const oc_octree* t, int l, int nbn, int cin, int cout, char* buf, size_t n) {
-  snprintf(buf, n, "k_conv_dws<%d, %s>", nbn,
-           t->N[l] * std::max(cin, cout) * 4 >= int64_t(1) << 32 ? "true" : "false");
+  snprintf(buf, n, "k_conv_dws<%d, %s>", nbn, rows_big(t, l, std::max(cin, cout)) ? "true" : "false");
 }
 
 }  // namespace oc

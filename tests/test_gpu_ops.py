@@ -6,7 +6,9 @@ row and weight-gradient entry, except the 5x5x5 64->64 layer of wide_d7,
 whose every row and entry is checked through random channel projections
 (each implied by the elementwise rule) beside exact contiguous tiles and
 exact entries of every (tap, 16 x 16 channel) block of dW."""
+import itertools
 import math
+import re
 
 import numpy as np
 import pytest
@@ -234,6 +236,31 @@ def test_conv_split_small_operands(K, cin, cout, a, b):
     dy = draw(b, N, cout)
     _, dw = oc.oc_conv_bwd(tree, l, K, 1, x, w, dy, need_dx=False)
     check("dw", dw, torch.stack([xp[nb[:, k]].t().contiguous() @ dy.double() for k in range(K3)]), N)
+
+
+def test_conv_kernel_names():
+    """oc_conv_kernel names instantiations that the library holds (template
+    arguments of the mangled names of its kernels), for every pass, type and
+    channel count, layers of 4 GiB and more among them."""
+    oc = _oc()
+    arg = {"Lb0E": "false", "Lb1E": "true"}
+    held = set()
+    with open(oc.lib_path(), "rb") as f:
+        for k, args in set(re.findall(rb"_ZN12_GLOBAL__N_1\d+(k_[a-z0-9_]+)I((?:L[ib]\d+E)+)E", f.read())):
+            parts = re.findall(r"L[ib]\d+E", args.decode())
+            held.add(f"{k.decode()}<{', '.join(arg.get(p) or p[2:-1] for p in parts)}>")
+    pts, nrm, offs = synth.make_points("deep_d8")
+    tree = oc.oc_build(torch.as_tensor(pts).cuda(), torch.as_tensor(nrm).cuda(), offs, 8, 2)
+    seen = set()
+    for l in (3, 5, 8):
+        for K, cin, cout, dt in itertools.product((3, 5), (3, 8, 16, 24, 64, 128, 1024), (5, 16, 64, 1024),
+                                                  (0, 1)):
+            for p in (0, 1, 2, 3):
+                name = oc.load().oc_conv_kernel(tree.handle, l, K, 1, dt, cin, cout, p).decode()
+                assert name in held or "<" not in name, (l, K, cin, cout, dt, p, name)
+                seen.add(name)
+    big = {n for n in seen if re.match(r"k_conv_(sp3|dws)<.*, true>$", n)}
+    assert tree.num(8) * 4096 >= 1 << 32 and len(big) >= 3, big
 
 
 def _median_us(f, n=15):
