@@ -238,6 +238,73 @@ def test_conv_split_small_operands(K, cin, cout, a, b):
     check("dw", dw, torch.stack([xp[nb[:, k]].t().contiguous() @ dy.double() for k in range(K3)]), N)
 
 
+def test_conv_split_4gib_backward():
+    """Both gradients with operands of 4 GiB and more: one 16-channel chunk is not
+    zero, so the input gradient is the small layer's bit for bit; the weight
+    gradient, whose groups are then summed in other chunks, against 64 bits in its
+    middle tap and against the small layer's in all."""
+    oc = _oc()
+    pts, nrm, offs = synth.make_points("deep_d8")
+    tree = oc.oc_build(torch.as_tensor(pts).cuda(), torch.as_tensor(nrm).cuda(), offs, 8, 2)
+    n = tree.num(8)
+    c = -(-(1 << 30) // n // 16) * 16 + 16
+    v = torch.zeros((n, c), device="cuda")
+    v[:, -16:] = torch.randn((n, 16), device="cuda")
+    vs = v[:, -16:].contiguous()
+    w = torch.randn((27, 4, c), device="cuda")
+    x = torch.randn((n, 4), device="cuda")
+    dx, _ = oc.oc_conv_bwd(tree, 8, 3, 1, x, w, v, need_dw=False)
+    dxs, _ = oc.oc_conv_bwd(tree, 8, 3, 1, x, w[:, :, -16:].contiguous(), vs, need_dw=False)
+    assert torch.equal(dx, dxs)
+    for cout in (16, 32):  # one and two blocks of columns
+        w = torch.randn((27, c, cout), device="cuda")
+        dy = torch.randn((n, cout), device="cuda")
+        name = oc.oc_conv_kernel(tree, 8, 3, 1, c, cout, 2)
+        assert name == f"k_conv_dws<{cout // 16}, true>"
+        _, dw = oc.oc_conv_bwd(tree, 8, 3, 1, v, w, dy, need_dx=False)
+        _, dws = oc.oc_conv_bwd(tree, 8, 3, 1, vs, w[:, -16:].contiguous(), dy, need_dx=False)
+        assert bool((dw[:, :-16] == 0).all())
+        ref = vs.double().t().contiguous() @ dy.double()
+        err = [float((d[13, -16:] - ref).norm() / ref.norm()) for d in (dw, dws)]
+        print(f"[4gib] dw {c}->{cout}: error {err[0]:.1e}, small layer {err[1]:.1e}", flush=True)
+        # a running sum of either half is rounded once a stage of 32 octants, at most
+        # n / 64 times: errors of either sign, below half an ulp of the sum
+        tol = math.sqrt(n / 64) * 2.0 ** -24
+        assert max(err) <= tol
+        assert float((dw[:, -16:] - dws).norm()) <= 2 * tol * float(dws.norm())
+
+
+def test_conv_split_4gib_pooled():
+    """The pooled forward on rows of 4 GiB and more (one chunk of 16 channels over
+    more than 2^26 octants): the plain forward then the pooling, bit for bit, and
+    the plain forward's rows against 64-bit sums."""
+    oc = _oc()
+    g = torch.Generator("cuda").manual_seed(241)
+    B, n = 48, 220_000
+    pts = torch.rand((B * n, 3), generator=g, device="cuda")
+    tree = oc.oc_build(pts, pts, torch.arange(B + 1, dtype=torch.int32) * n, 8, 2)
+    N = tree.num(8)
+    print(f"[4gib] {N} rows", flush=True)
+    assert N * 64 >= 1 << 32
+    assert oc.oc_conv_kernel(tree, 8, 3, 1, 16, 4, 3) == "k_conv_sp3<1, 8, false, true, true>"
+    x = torch.randn((N, 16), generator=g, device="cuda")
+    w = torch.randn((27, 16, 4), generator=g, device="cuda")
+    y = oc.oc_conv_fwd(tree, 8, 3, 1, x, w, relu=True)
+    p, sw = oc.oc_conv_pool_fwd(tree, 8, 3, x, w)
+    pr, swr = oc.oc_pool_fwd(tree, 8, y)
+    assert torch.equal(p, pr) and torch.equal(sw, swr)
+    at = torch.randint(0, N // 8, (500,), generator=g, device="cuda")
+    at[:2] = torch.tensor([0, N // 8 - 1])
+    nbr, want = tree.nbr(8)[at].long(), torch.zeros((500, 8, 4), dtype=torch.float64, device="cuda")
+    for k, c in itertools.product(range(27), range(8)):
+        v = [(c >> s & 1) + d - 1 for s, d in ((2, k // 9), (1, k // 3 % 3), (0, k % 3))]
+        e = nbr[:, ((v[0] >> 1) + 1) * 9 + ((v[1] >> 1) + 1) * 3 + (v[2] >> 1) + 1]
+        rows = x[e.clamp(min=0) + 4 * (v[0] & 1) + 2 * (v[1] & 1) + (v[2] & 1)].double()
+        want[:, c] += (rows * (e >= 0)[:, None]) @ w[k].double()
+    got = y.view(-1, 8, 4)[at].double()
+    assert float((got - want.clamp(min=0)).norm()) <= 1e-6 * float(want.norm())
+
+
 def test_conv_kernel_names():
     """oc_conv_kernel names instantiations that the library holds (template
     arguments of the mangled names of its kernels), for every pass, type and
