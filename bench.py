@@ -87,6 +87,24 @@ PEAK = {  # MI355X published peaks
     "fp32_TFLOPs": 157.3,
     "bf16_TFLOPs": 2500.0,
 }
+# Kernels that form an fp32 product from six bf16 products (three bf16 parts an
+# operand): a sixth of the bf16 peak bounds them, not the fp32 one.
+PEAK["fp32_split_TFLOPs"] = round(PEAK["bf16_TFLOPs"] / 6, 1)
+
+
+def mfma_peak(kernel, bf16):
+    """Peak TFLOP/s of the matrix instructions that a convolution kernel uses
+    (its name as oc_conv_kernel gives it)."""
+    if kernel.startswith(("k_conv_sp3<", "k_conv_dws<")) or (
+            kernel.startswith(("k_conv_bfw<", "k_conv_bf_dw<")) and kernel.endswith(" true>")):
+        return PEAK["fp32_split_TFLOPs"]
+    return PEAK["bf16_TFLOPs" if bf16 else "fp32_TFLOPs"]
+
+
+def mean_peak(parts):
+    """Peak of several kernels' work together: (work, peak) of each."""
+    return sum(w for w, _ in parts) / sum(w / p for w, p in parts)
+
 
 # Per-kernel-class accounting: "flops" (MFMA-bound) or "bytes" (HBM-bound).
 BOUND = {
@@ -322,12 +340,15 @@ def summarize_mfma(pmc_dir, prof_dir):
               f"{100 * frac:.1f}% | {100 * lw:.1f}% | {bc:.2f} |")
 
 
-def op_rate(cls, work, us, bf16):
+def op_rate(cls, work, us, bf16, peak=None):
     """Achieved rate of an op class from its algorithmic work (flops of a conv
-    class, HBM bytes otherwise) and its time per step, against the peak."""
+    class, HBM bytes otherwise) and its time per step, against the peak (of a
+    conv class: of its kernels' matrix instructions; by default the fp32 or bf16
+    ones)."""
     if cls.startswith(("conv", "deconv")):
         a = work / (us * 1e-6) / 1e12
-        peak, unit = PEAK["bf16_TFLOPs" if bf16 else "fp32_TFLOPs"], "TFLOP/s"
+        peak = round(peak, 1) if peak else PEAK["bf16_TFLOPs" if bf16 else "fp32_TFLOPs"]
+        unit = "TFLOP/s"
     else:
         a = work / (us * 1e-6) / 1e9
         peak, unit = PEAK["hbm_GBps"], "GB/s"
@@ -411,6 +432,7 @@ def summarize_trace(prof_dir, prof_log):
         us[cls] = us.get(cls, 0.0) + tot / (builds if cls == "build" else nsteps)
         names.setdefault(cls, []).append(k)
     bf16 = any(L.op == "conv" and L.dtype == "bf16" for L in wl.layers)
+    conv_peak = line.get("ops", {}).get("conv_fwd_bwd", {}).get("peak")
     flops, _ = acc.conv_flops()
     # a pooling run inside the convolution below it (conv + pool calls) has no
     # forward kernel of its own: its bytes are not the pooling kernels' work
@@ -434,7 +456,7 @@ def summarize_trace(prof_dir, prof_log):
           "share of peak |")
     print("|---|---|---|---|---|---|")
     for label, cls, work, t in rows:
-        r = op_rate(cls, work, t, bf16)
+        r = op_rate(cls, work, t, bf16, conv_peak)
         w = f"{work / 1e9:.3f} GFLOP" if cls == "conv" else f"{work / 1e6:.2f} MB"
         print(f"| {label} | {t:.1f} | {w} | {r['achieved']:.1f} {r['unit']} | {r['peak']:g} | "
               f"{100 * r['frac']:.1f}% |")
@@ -1339,7 +1361,7 @@ def main():
     if bound == "mfma":
         achieved = per_launch_work / (per_launch_ms * 1e-3) / 1e12
         bf16 = any(L is not None and L.dtype == "bf16" for _, _, L, _ in step.events[dominant])
-        peak, unit = PEAK["bf16_TFLOPs" if bf16 else "fp32_TFLOPs"], "TFLOP/s"
+        peak, unit = mfma_peak(dominant, bf16), "TFLOP/s"
     else:
         achieved = per_launch_work / (per_launch_ms * 1e-3) / 1e9
         peak, unit = PEAK["hbm_GBps"], "GB/s"
@@ -1353,20 +1375,24 @@ def main():
         roofline["traffic_detail"] = traffic
 
     # every op class's main kernels in the warmup, against its work
-    ops = {}
-    for v in warm.values():
+    ops, peaks = {}, {}
+    bf16 = any(L.op == "conv" and L.dtype == "bf16" for L in wl.layers)
+    for k, v in warm.items():
         c = ops.setdefault(step.op_class(v["op"]), [0.0, 0.0])
         c[0] += v["ms"] * 1e3 / nwarm
         c[1] += v["work"] / nwarm
-    bf16 = any(L.op == "conv" and L.dtype == "bf16" for L in wl.layers)
+        if v["work"] > 0 and v["op"].startswith(("conv", "deconv")):
+            peaks.setdefault(v["op"], []).append((v["work"], mfma_peak(k, bf16)))
+    conv_peak = mean_peak([p for ps in peaks.values() for p in ps]) if peaks else None
     # the build's events also span host work (the wait for its counts): its
     # rate comes from a kernel trace (--summarize-trace) instead
     ops.pop("build", None)
-    ops_out = {c: op_rate(c, w, t, bf16) for c, (t, w) in sorted(ops.items()) if t > 0 and w > 0}
+    ops_out = {c: op_rate(c, w, t, bf16, mean_peak(peaks[c]) if c in peaks else None)
+               for c, (t, w) in sorted(ops.items()) if t > 0 and w > 0}
     conv = [v for c, v in ops.items() if c.startswith(("conv", "deconv"))]
     if conv:
         ops_out["conv_fwd_bwd"] = op_rate("conv", sum(w for _, w in conv),
-                                          sum(t for t, _ in conv), bf16)
+                                          sum(t for t, _ in conv), bf16, conv_peak)
     # every kernel of the conv passes (split sums, ReLU masks, operand
     # conversions and gathers included), per layer and in total
     layers, tot_us, tot_work = [], 0.0, 0.0
@@ -1375,16 +1401,18 @@ def main():
             continue
         tags = (("conv_fwd", "conv_bwd_data", "conv_bwd_weight") if L.op == "conv" else
                 ("deconv_fwd", "deconv_bwd_data", "deconv_bwd_weight"))
-        us, work = {}, 0.0
+        us, work, parts = {}, 0.0, []
         for tag in tags:
             a = allk.get((li, tag))
             if a and a[1]:
                 us[tag.split("_", 1)[1]] = round(a[0] * 1e3 / a[1], 2)
                 work += step.work(tag, L)
+                parts.append((step.work(tag, L),
+                              mfma_peak(step.kname.get((li, tag), tag), L.dtype == "bf16")))
         t = sum(us.values())
         if t <= 0:
             continue
-        r = op_rate("conv", work, t, L.dtype == "bf16")
+        r = op_rate("conv", work, t, L.dtype == "bf16", mean_peak(parts))
         layers.append({"layer": li, "op": L.op, "depth": L.depth, "ksize": L.ksize,
                        "stride": L.stride, "cin": L.cin, "cout": L.cout, "dtype": L.dtype,
                        "rows": step._n_conv(L), "us": us, "us_total": round(t, 2),
@@ -1398,7 +1426,7 @@ def main():
     if a and a[1]:
         tot_us += a[0] * 1e3 / a[1]
     if tot_us > 0:
-        ops_out["conv_fwd_bwd_all"] = op_rate("conv", tot_work, tot_us, bf16)
+        ops_out["conv_fwd_bwd_all"] = op_rate("conv", tot_work, tot_us, bf16, conv_peak)
 
     if args.layers:
         for key, v in sorted(warm.items(), key=lambda kv: -kv[1]["ms"]):

@@ -15,8 +15,8 @@ import synth  # noqa: E402
 
 
 def test_short_name_strips_namespace_and_arguments():
-    n = "void (anonymous namespace)::k_conv_tile3<4, 8, false>(int const*, long, float const*)"
-    assert bench._short_name(n) == "k_conv_tile3<4, 8, false>"
+    n = "void (anonymous namespace)::k_conv_sp3<4, 8, false, false, false>(int const*, long, float const*)"
+    assert bench._short_name(n) == "k_conv_sp3<4, 8, false, false, false>"
     assert bench._short_name("k_sum_split(float const*, int)") == "k_sum_split"
     # template arguments that hold parentheses stay whole
     assert bench._short_name("k_x<(anonymous namespace)::T(1)>(int)") == "k_x<T(1)>"
@@ -33,13 +33,29 @@ def test_op_rate_units_and_peaks():
     assert r["frac"] == pytest.approx(0.1)
 
 
+def test_peak_of_split_products():
+    """fp32 products formed from six bf16 products are priced against a sixth of
+    the bf16 peak; a class of several kernels, each share against its own."""
+    split = 2500.0 / 6
+    for k in ("k_conv_sp3<4, 8, false, true, false>", "k_conv_dws<2, false>",
+              "k_conv_bfw<5, 2, true, 8, 4, true>", "k_conv_bf_dw<5, 10, 4, 4, true>"):
+        assert bench.mfma_peak(k, False) == pytest.approx(split, rel=1e-3)
+    assert bench.mfma_peak("k_conv_bfw<5, 2, true, 8, 4, false>", True) == 2500.0
+    assert bench.mfma_peak("k_cin_fwd<3, true>", False) == 157.3
+    assert bench.mfma_peak("k_conv_tile<5, 1, 1, 2, 4, true, true>", False) == 157.3
+    # 1 ms at 157.3 and 1 ms at 2500 TFLOP/s
+    assert bench.mean_peak([(157.3, 157.3), (2500.0, 2500.0)]) == pytest.approx((157.3 + 2500) / 2)
+    r = bench.op_rate("conv_fwd", 2e9, 10.0, False, split)  # 200 TFLOP/s
+    assert r["peak"] == 416.7 and r["frac"] == pytest.approx(200 / 416.7, abs=1e-4)
+
+
 def test_trace_classes():
     assert bench.trace_class("k_quant") == "build"
     assert bench.trace_class("k_leaf_mean") == "build"
     assert bench.trace_class("k_route_down<4>") == "pool"
-    assert bench.trace_class("k_conv_dwt<false, 16, 2, 4, true, 2>") == "conv_main"
+    assert bench.trace_class("k_conv_dwt<16, 2, 4, true>") == "conv_main"
     assert bench.trace_class("k_cin_fwd<3, true>") == "conv_main"
-    assert bench.trace_class("k_conv_tile3<2, 8, false, true>") == "conv_main"
+    assert bench.trace_class("k_conv_sp3<2, 8, false, true, false>") == "conv_main"
     assert bench.trace_class("k_sum_parts<16, 4>") == "conv_helper"
     assert bench.trace_class("k_sum_split_pool") == "conv_helper"
     assert bench.trace_class("k_sr_table") == "conv_helper"
@@ -79,7 +95,7 @@ def test_summarize_trace(tmp_path, capsys):
     d = tmp_path / "prof"
     d.mkdir()
     # 5 network steps (warmup 2 + 3 timed), 6 builds; times in ns
-    rows = [("void (anonymous namespace)::k_conv_tile3<4, 8, false>(int)", 15, 15 * 40000),
+    rows = [("void (anonymous namespace)::k_conv_sp3<4, 8, false, false, false>(int)", 15, 15 * 40000),
             ("k_sum_split(float const*)", 10, 10 * 5000),
             ("k_pool_fwd<4>(float const*)", 20, 20 * 4000),
             ("k_quant(float const*)", 6, 6 * 7000),
@@ -100,7 +116,7 @@ def test_summarize_trace(tmp_path, capsys):
     tf = flops / 120e-6 / 1e12
     assert f"{tf:.1f} TFLOP/s" in out
     assert "other kernels (at::native::copy)" in out
-    assert "`k_conv_tile3<4, 8, false>` | 15 | 40.00 |" in out
+    assert "`k_conv_sp3<4, 8, false, false, false>` | 15 | 40.00 |" in out
 
 
 def test_accounting_of_pool_backward():
