@@ -726,6 +726,9 @@ class Step(Accounting):
                 b.record()  # instantiates the events
                 self.oc.oc_profile_next(a, b)
                 r = fn()
+                # an op that launched no main kernel (the deferred sums) leaves
+                # the pair pending, and the next step's first kernel would take it
+                self.oc.oc_profile_next(None, None)
             else:
                 a.record()
                 r = fn()

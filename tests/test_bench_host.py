@@ -49,6 +49,22 @@ def test_peak_of_split_products():
     assert r["peak"] == 416.7 and r["frac"] == pytest.approx(200 / 416.7, abs=1e-4)
 
 
+def test_profile_events_do_not_outlive_their_op():
+    """The pair of events armed for an op is cleared after it, also when the op
+    launched no main kernel: the next op's kernel does not take it."""
+    from types import SimpleNamespace
+
+    armed = []
+    step = bench.Step.__new__(bench.Step)
+    step.wl, step.kname, step.calls = synth.WORKLOADS["net_d5"], {}, None
+    step.events, step.traced, step.rotate = {}, {"*"}, 0
+    event = lambda **k: SimpleNamespace(record=lambda: None)  # noqa: E731
+    step.torch = SimpleNamespace(cuda=SimpleNamespace(Event=event))
+    step.oc = SimpleNamespace(oc_profile_next=lambda a, b: armed.append((a, b)))
+    assert step._run("dw_sum", None, lambda: 7) == 7
+    assert len(armed) == 2 and armed[0][0] is not None and armed[1] == (None, None)
+
+
 def test_trace_classes():
     assert bench.trace_class("k_quant") == "build"
     assert bench.trace_class("k_leaf_mean") == "build"
