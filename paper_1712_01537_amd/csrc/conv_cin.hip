@@ -88,17 +88,6 @@ __device__ __forceinline__ v4f mfma4(float a, float b, v4f c) {
   return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
 
-// Lane l's accumulator D[4(l/16)+j][l%16] handed over so that lane l holds
-// D[4(l%4)+j][l/4] (four consecutive output channels of one row).
-__device__ __forceinline__ v4f store_order(v4f d, int lane) {
-  const int src = (((lane & 3) << 4) + (lane >> 2)) << 2;
-  v4f r;
-#pragma unroll
-  for (int j = 0; j < 4; ++j)
-    r[j] = __int_as_float(__builtin_amdgcn_ds_bpermute(src, __float_as_int(d[j])));
-  return r;
-}
-
 // Slot of position (px, py, pz) in {0..3}^3 (relative to the first child of
 // group gg minus one) in the group's 64-slot tile: 16 px + 4 py + pz, or with
 // SWZ the z bits XOR-ed with (2 gg + (px & 1)).  The forward's reads take one
@@ -311,7 +300,7 @@ __global__ __launch_bounds__(TB) void k_cin_fwd(const int32_t* __restrict__ nbr,
       for (int j = 0; j < D; ++j) pq[j] = pq[j + 1];
     } else {
       // lane l: row l / 4 of the tile, channels n0 + 4 (l % 4) ..
-      acc = store_order(acc, lane);
+      acc = oc::store_order(acc, lane);
       const int64_t row = 16 * t + (lane >> 2);
       float* dst =
           row < 8 * ngroups ? y + row * cout + n0 + 4 * (lane & 3) : g_cin_dummy + 4 * lane;

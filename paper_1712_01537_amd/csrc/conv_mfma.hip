@@ -1,4 +1,7 @@
-// fp32 octree convolution on the matrix cores (v_mfma_f32_16x16x4_f32).
+// fp32 octree convolution on the matrix cores (v_mfma_f32_16x16x4_f32): the
+// layers that the kernels on three bf16 parts (conv_split.hip; K = 5:
+// conv_bf16.hip) do not take, the launch rules of all, and the sums of their
+// partial results.
 //
 // Stride-1 forward and input gradient share one implicit-GEMM kernel that
 // works on sibling groups.  The eight children of a group sit at the corners
@@ -17,9 +20,7 @@
 // MFMA operand layout (16x16x4, fp32): lane l supplies A[l%16][l/16] and
 // B[l/16][l%16] and receives D[4(l/16)+j][l%16] in accumulator j.  Rows of
 // A are 16 output octants (two sibling groups), columns of B 16 output
-// channels.  With V = 4, lane group q supplies reduction channels 4q..4q+3
-// of a 16-channel block to four consecutive MFMAs (channel 4q+s to the s-th),
-// so one 16-byte LDS read per lane feeds four MFMAs.
+// channels.
 //
 // The weight gradient dW[k][c][n] = sum_i x[nb(i,k)][c] dY[i][n] is a GEMM
 // with M = (tap, channel) pairs, N = output channels and the octants as the
@@ -66,18 +67,6 @@ __device__ __forceinline__ void lds_load12(const void* src, uint32_t lds) {
   asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx3 %1, off" ::"s"(lds), "v"(src)
                : "memory", "m0");
 }
-// A 16x16 MFMA result held as D[4(l/16)+j][l%16] in lane l (j = 0..3) is
-// handed over so that lane l holds D[4(l%4)+j][l/4]: with rows l%16 of the
-// result as output rows, consecutive lanes then store consecutive 16 bytes.
-__device__ __forceinline__ v4f store_order(v4f d, int lane) {
-  const int src = (((lane & 3) << 4) + (lane >> 2)) << 2;  // byte lane index
-  v4f r;
-#pragma unroll
-  for (int j = 0; j < 4; ++j)
-    r[j] = __int_as_float(__builtin_amdgcn_ds_bpermute(src, __float_as_int(d[j])));
-  return r;
-}
-
 // s_waitcnt vmcnt(0): all of this wave's vector memory operations are done.
 __device__ __forceinline__ void vm_wait0() { __builtin_amdgcn_s_waitcnt(0x0F70); }
 
@@ -85,31 +74,18 @@ __device__ __forceinline__ v4f mfma4(float a, float b, v4f c) {
   return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
 
-// Row at depth l of tile position (px,py,pz) of a group whose 27-entry
-// parent-neighbour row is nb, or -1.  Positions are offsets +R from the
-// group's first child, per axis in [-R, 1+R].
-template <int R>
-__device__ __forceinline__ int32_t tile_src(const int32_t* __restrict__ nb, int px, int py,
-                                            int pz) {
-  const int ux = px - R, uy = py - R, uz = pz - R;
-  const int32_t base = nb[((ux >> 1) + 1) * 9 + ((uy >> 1) + 1) * 3 + ((uz >> 1) + 1)];
-  return base < 0 ? -1 : base + 4 * (ux & 1) + 2 * (uy & 1) + (uz & 1);
-}
-
 // ---------------------------------------------------------------------------
 // Stride-1 implicit GEMM over group tiles.
-//   K   kernel size (3 or 5);  V  channels per lane per LDS read (1 or 4);
-//   MR, NR  16-row / 16-column MFMA blocks per wave;  WM  waves along rows
-//   (WAVES / WM along columns);  FLIP  false: forward, W[k][c][n] at
-//   (k*kk + c)*nn + n;  true: input gradient, W'[k][c][n] = W[K3-1-k][n][c].
+//   K   kernel size (3 or 5);  MR, NR  16-row / 16-column MFMA blocks per
+//   wave;  WM  waves along rows (WAVES / WM along columns);  FLIP  false:
+//   forward, W[k][c][n] at (k*kk + c)*nn + n;  true: input gradient,
+//   W'[k][c][n] = W[K3-1-k][n][c].
 // A workgroup computes BM = 16 WM MR rows (BM / 8 sibling groups) by
-// BN = 16 (WAVES/WM) NR columns.  Per chunk of CC reduction channels it
+// BN = 16 (WAVES/WM) NR columns.  Per chunk of CC = 4 reduction channels it
 // gathers the groups' (K+1)^3 tiles into LDS, then walks the taps in slabs
-// of TSL taps, staging each slab's weights as Bt[tap][n][c] so that a lane
-// reads its V channels with one LDS load.  Group tiles are stored with two
-// padding rows per x-slab and rows of RS = CC + 4 floats, which puts the
-// eight children of a group (and 16 consecutive weight columns) on distinct
-// LDS banks.
+// of TSL taps, staging each slab's weights as Bt[tap][n][c].  Group tiles are
+// stored with two padding rows per x-slab, which puts the eight children of a
+// group on distinct LDS banks.
 // Workgroups are persistent over a contiguous range of row tiles.  The loads
 // of the next step (the next weight slab; at the end of a chunk also the next
 // chunk's or the next tile's group tiles) are issued before each step's
@@ -123,7 +99,7 @@ __device__ __forceinline__ int32_t tile_src(const int32_t* __restrict__ nb, int 
 // applied if relu) goes to out; otherwise split z writes its partial sum to
 // part[z][row][n] and k_sum_split finishes.
 // gate != NULL: the launch does its work only when *gate is set.
-template <int K, int V, int MR, int NR, int WM, bool FLIP, bool VEC>
+template <int K, int MR, int NR, int WM, bool FLIP, bool VEC>
 __global__ __launch_bounds__(TB) void k_conv_tile(const int32_t* __restrict__ nbr, int64_t ngroups,
                                                   const float* __restrict__ x, int kk,
                                                   const float* __restrict__ w, int nn,
@@ -135,23 +111,21 @@ __global__ __launch_bounds__(TB) void k_conv_tile(const int32_t* __restrict__ nb
   constexpr int R = (K - 1) / 2, S = K + 1, K2 = K * K, K3 = K2 * K, S3 = S * S * S;
   constexpr int PX = S * S + 2;  // tile rows per x-slab (two padding rows)
   constexpr int P3 = S * PX;     // tile rows per group
-  constexpr int CC = 4 * V;
-  constexpr int F4 = CC / 4;
-  constexpr int RS = V == 4 ? CC + 4 : CC;
+  constexpr int CC = 4;  // reduction channels of a chunk, floats of an LDS row
   constexpr int BM = WM * MR * 16, BN = WN * NR * 16, GPB = BM / 8;
-  constexpr int TSL = (V == 1 && K == 3) ? K3 : K2;  // taps per weight slab
+  constexpr int TSL = K == 3 ? K3 : K2;  // taps per weight slab
   constexpr int NSL = K3 / TSL;                     // slabs per channel chunk
   // Staging of the next step's global loads in registers.  Tile: each pass
-  // covers GPP groups, thread -> fixed (group of the pass, position, channel
-  // quad); NA passes.  Weight slab: (tap, column, channel quad) elements,
-  // float4 along the contiguous axis of W; NB passes.
-  constexpr int GPP = TB / (S3 * F4) > 0 ? TB / (S3 * F4) : 1;
+  // covers GPP groups, thread -> fixed (group of the pass, position); NA
+  // passes.  Weight slab: (tap, column) or (tap, channel, column quad)
+  // elements, float4 along the contiguous axis of W; NB passes.
+  constexpr int GPP = TB / S3 > 0 ? TB / S3 : 1;
   constexpr int NA = GPB / GPP;
-  constexpr int NB = (TSL * BN * F4 + TB - 1) / TB;
-  static_assert(S3 * F4 <= TB && GPB % GPP == 0, "tile staging must cover every position");
+  constexpr int NB = (TSL * BN + TB - 1) / TB;
+  static_assert(S3 <= TB && GPB % GPP == 0, "tile staging must cover every position");
   static_assert(NA <= 32 && NB <= 32, "validity bits fit a word");
-  __shared__ __attribute__((aligned(16))) float At[GPB * P3 * RS];
-  __shared__ __attribute__((aligned(16))) float Bt[TSL * BN * RS];
+  __shared__ __attribute__((aligned(16))) float At[GPB * P3 * CC];
+  __shared__ __attribute__((aligned(16))) float Bt[TSL * BN * CC];
 
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int li = lane & 15, q = lane >> 4;
@@ -186,11 +160,11 @@ __global__ __launch_bounds__(TB) void k_conv_tile(const int32_t* __restrict__ nb
 #pragma unroll
     for (int nr = 0; nr < NR; ++nr) acc[mr][nr] = v4f{0.f, 0.f, 0.f, 0.f};
 
-  // this thread's tile element: group a_g + GPP i, position a_p, channels 4 a_f..
-  const bool a_on = tid < GPP * S3 * F4;
-  const int a_g = tid / (S3 * F4), a_p = (tid / F4) % S3, a_f = tid % F4;
+  // this thread's tile element: group a_g + GPP i, position a_p
+  const bool a_on = tid < GPP * S3;
+  const int a_g = tid / S3, a_p = tid % S3;
   const int a_px = a_p / (S * S), a_py = (a_p / S) % S, a_pz = a_p % S;
-  const int a_lds = (a_g * P3 + a_px * PX + a_py * S + a_pz) * RS + 4 * a_f;
+  const int a_lds = (a_g * P3 + a_px * PX + a_py * S + a_pz) * CC;
   // the position's parent-offset slot in the 27-entry neighbour row, and child
   const int a_ux = a_px - R, a_uy = a_py - R, a_uz = a_pz - R;
   const int a_slot = ((a_ux >> 1) + 1) * 9 + ((a_uy >> 1) + 1) * 3 + ((a_uz >> 1) + 1);
@@ -218,32 +192,30 @@ __global__ __launch_bounds__(TB) void k_conv_tile(const int32_t* __restrict__ nb
   uint32_t aok = 0;
   int a_c0 = 0;
   auto load_a = [&](int c0) {
-    const int ch = c0 + 4 * a_f;
     a_c0 = c0;
     aok = 0;
 #pragma unroll
     for (int i = 0; i < NA; ++i) {
-      const bool live = ((okc >> i) & 1) && nbc[i] >= 0 && ch < kk;
-      const int64_t off = live ? (int64_t)(nbc[i] + a_coff) * kk + ch : 0;
+      const bool live = ((okc >> i) & 1) && nbc[i] >= 0 && c0 < kk;
+      const int64_t off = live ? (int64_t)(nbc[i] + a_coff) * kk + c0 : 0;
       if constexpr (VEC) {
         ra[i] = *reinterpret_cast<const v4f*>(x + off);
       } else {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) ra[i][j] = x[off + (live && ch + j < kk ? j : 0)];
+        for (int j = 0; j < 4; ++j) ra[i][j] = x[off + (live && c0 + j < kk ? j : 0)];
       }
       aok |= (uint32_t)live << i;
     }
   };
   auto store_a = [&]() {
     if (!a_on) return;
-    const int ch = a_c0 + 4 * a_f;
 #pragma unroll
     for (int i = 0; i < NA; ++i) {
       v4f v = ra[i];
       const bool live = (aok >> i) & 1;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) v[j] = live && ch + j < kk ? v[j] : 0.f;
-      *reinterpret_cast<v4f*>(&At[a_lds + i * GPP * P3 * RS]) = v;
+      for (int j = 0; j < 4; ++j) v[j] = live && a_c0 + j < kk ? v[j] : 0.f;
+      *reinterpret_cast<v4f*>(&At[a_lds + i * GPP * P3 * CC]) = v;
     }
   };
 
@@ -257,18 +229,18 @@ __global__ __launch_bounds__(TB) void k_conv_tile(const int32_t* __restrict__ nb
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
       const int e = tid + i * TB;
-      if constexpr (FLIP) {  // (t, n, f): 4 consecutive channels of W[K3-1-k][n]
-        const int f = e % F4, n = (e / F4) % BN, t = e / (F4 * BN);
-        const int gn = n0 + n, ch = c0 + 4 * f;
-        const bool live = t < TSL && gn < nn && ch < kk;
-        const int64_t off = live ? ((int64_t)(K3 - 1 - (k0 + t)) * nn + gn) * kk + ch : 0;
+      if constexpr (FLIP) {  // (t, n): 4 consecutive channels of W[K3-1-k][n]
+        const int n = e % BN, t = e / BN;
+        const int gn = n0 + n;
+        const bool live = t < TSL && gn < nn && c0 < kk;
+        const int64_t off = live ? ((int64_t)(K3 - 1 - (k0 + t)) * nn + gn) * kk + c0 : 0;
         if constexpr (VEC) {
           rb[i] = *reinterpret_cast<const float4*>(w + off);
         } else {
           rb[i].x = w[off];
-          rb[i].y = w[off + (live && ch + 1 < kk ? 1 : 0)];
-          rb[i].z = w[off + (live && ch + 2 < kk ? 2 : 0)];
-          rb[i].w = w[off + (live && ch + 3 < kk ? 3 : 0)];
+          rb[i].y = w[off + (live && c0 + 1 < kk ? 1 : 0)];
+          rb[i].z = w[off + (live && c0 + 2 < kk ? 2 : 0)];
+          rb[i].w = w[off + (live && c0 + 3 < kk ? 3 : 0)];
         }
         bok |= (uint32_t)live << i;
       } else {  // (t, cc, n4): 4 consecutive columns of W[k][ch]
@@ -294,23 +266,22 @@ __global__ __launch_bounds__(TB) void k_conv_tile(const int32_t* __restrict__ nb
       const int e = tid + i * TB;
       const bool live = (bok >> i) & 1;
       if constexpr (FLIP) {
-        const int f = e % F4, n = (e / F4) % BN, t = e / (F4 * BN);
-        const int ch = b_c0 + 4 * f;
+        const int n = e % BN, t = e / BN;
         if (t < TSL) {
           const float4 v = rb[i];
-          *reinterpret_cast<float4*>(&Bt[(t * BN + n) * RS + 4 * f]) =
-              float4{live ? v.x : 0.f, live && ch + 1 < kk ? v.y : 0.f,
-                     live && ch + 2 < kk ? v.z : 0.f, live && ch + 3 < kk ? v.w : 0.f};
+          *reinterpret_cast<float4*>(&Bt[(t * BN + n) * CC]) =
+              float4{live ? v.x : 0.f, live && b_c0 + 1 < kk ? v.y : 0.f,
+                     live && b_c0 + 2 < kk ? v.z : 0.f, live && b_c0 + 3 < kk ? v.w : 0.f};
         }
       } else {
         const int n4 = e % (BN / 4), cc = (e / (BN / 4)) % CC, t = e / (BN / 4 * CC);
         const int gn = n0 + 4 * n4;
         if (t < TSL) {
-          float* d = &Bt[(t * BN + 4 * n4) * RS + cc];
+          float* d = &Bt[(t * BN + 4 * n4) * CC + cc];
           d[0] = live ? rb[i].x : 0.f;
-          d[RS] = live && gn + 1 < nn ? rb[i].y : 0.f;
-          d[2 * RS] = live && gn + 2 < nn ? rb[i].z : 0.f;
-          d[3 * RS] = live && gn + 3 < nn ? rb[i].w : 0.f;
+          d[CC] = live && gn + 1 < nn ? rb[i].y : 0.f;
+          d[2 * CC] = live && gn + 2 < nn ? rb[i].z : 0.f;
+          d[3 * CC] = live && gn + 3 < nn ? rb[i].w : 0.f;
         }
       }
     }
@@ -321,35 +292,15 @@ __global__ __launch_bounds__(TB) void k_conv_tile(const int32_t* __restrict__ nb
     for (int tp = 0; tp < TSL; ++tp) {
       const int k = k0 + tp;
       const int toff = (k / K2) * PX + ((k / K) % K) * S + k % K;
-      float a[MR][V], b[NR][V];
+      float a[MR], b[NR];
 #pragma unroll
-      for (int mr = 0; mr < MR; ++mr) {
-        const float* tpp = &At[(tbase[mr] + toff) * RS + V * q];
-        if constexpr (V == 4) {
-          const v4f u = *reinterpret_cast<const v4f*>(tpp);
+      for (int mr = 0; mr < MR; ++mr) a[mr] = At[(tbase[mr] + toff) * CC + q];
 #pragma unroll
-          for (int j = 0; j < 4; ++j) a[mr][j] = u[j];
-        } else {
-          a[mr][0] = tpp[0];
-        }
-      }
+      for (int nr = 0; nr < NR; ++nr) b[nr] = Bt[(tp * BN + bcol[nr]) * CC + q];
 #pragma unroll
-      for (int nr = 0; nr < NR; ++nr) {
-        const float* bp = &Bt[(tp * BN + bcol[nr]) * RS + V * q];
-        if constexpr (V == 4) {
-          const v4f u = *reinterpret_cast<const v4f*>(bp);
+      for (int mr = 0; mr < MR; ++mr)
 #pragma unroll
-          for (int j = 0; j < 4; ++j) b[nr][j] = u[j];
-        } else {
-          b[nr][0] = bp[0];
-        }
-      }
-#pragma unroll
-      for (int j = 0; j < V; ++j)
-#pragma unroll
-        for (int mr = 0; mr < MR; ++mr)
-#pragma unroll
-          for (int nr = 0; nr < NR; ++nr) acc[mr][nr] = mfma4(a[mr][j], b[nr][j], acc[mr][nr]);
+        for (int nr = 0; nr < NR; ++nr) acc[mr][nr] = mfma4(a[mr], b[nr], acc[mr][nr]);
     }
   };
 
@@ -488,7 +439,7 @@ __global__ __launch_bounds__(TB) void k_conv_cin(const int32_t* __restrict__ nbr
     acc = mfma4(wb[k * 64], xb[4 * (16 * (k / 9) + 4 * ((k / 3) % 3) + k % 3)], acc);
   // accumulator j of lane l: output channel n0 + 4(l/16) + j, row l % 16;
   // after store_order lane l writes row l/4, channels n0 + 4(l%4)..
-  acc = store_order(acc, lane);
+  acc = oc::store_order(acc, lane);
   const int64_t row = 8 * g0 + 16 * wave + (lane >> 2);
   const int n = n0 + 4 * (lane & 3);
   if (row < 8 * ngroups && n < nn) {
@@ -1194,7 +1145,7 @@ void sum_parts(const float* part, int np, int64_t n, float* out, hipStream_t s) 
 // Launch-shape selection.
 
 struct TileCfg {
-  int V, MR, NR, WM, splits, cps;
+  int MR, NR, WM, splits, cps;
   bool VEC;
   bool v2;  // k_conv_sp3: K = 3, 16-channel chunks, one chunk per split
 };
@@ -1209,7 +1160,7 @@ TileCfg pick_tile(int K, int64_t G, int kk, int nn) {
     c.splits = oc::sp3_pick(G, kk, nn).splits;
     return c;
   }
-  c.V = 1, c.WM = 4;
+  c.WM = 4;
   if (K == 3) {
     c.MR = 2, c.NR = 1;  // 128 x 16
   } else {
@@ -1217,7 +1168,7 @@ TileCfg pick_tile(int K, int64_t G, int kk, int nn) {
   }
   const int BM = 16 * c.WM * c.MR, BN = 16 * (WAVES / c.WM) * c.NR;
   const int64_t tiles = oc::cdiv(G, BM / 8) * oc::cdiv(nn, BN);
-  const int chunks = (int)oc::cdiv(kk, 4 * c.V);
+  const int chunks = (int)oc::cdiv(kk, 4);
   int splits = 1;
   while (tiles * splits < 2048 && splits * 2 <= chunks) splits *= 2;
   c.cps = (int)oc::cdiv(chunks, splits);
@@ -1225,11 +1176,11 @@ TileCfg pick_tile(int K, int64_t G, int kk, int nn) {
   return c;
 }
 
-template <int K, int V, int MR, int NR, int WM, bool FLIP, bool VEC>
+template <int K, int MR, int NR, int WM, bool FLIP, bool VEC>
 void launch_tile(const oc_octree* t, int l, const TileCfg& c, const float* x, int kk,
                  const float* w, int nn, float* out, int relu, float* part, hipStream_t s,
                  const RouteOut* ro, const uint32_t* gate) {
-  const auto kernel = k_conv_tile<K, V, MR, NR, WM, FLIP, VEC>;
+  const auto kernel = k_conv_tile<K, MR, NR, WM, FLIP, VEC>;
   static const int occ = [&] {
     int n = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, kernel, TB, 0) != hipSuccess || n < 1)
@@ -1267,7 +1218,7 @@ void dispatch_tile(const oc_octree* t, int l, int K, const float* x, int kk, con
     // the launch below then works out again, in one split, what is not finite
     gate = oc::sp5_fwd(t, l, FLIP, x, kk, w, nn, out, relu, part, s);
     c.splits = 1;
-    c.cps = (int)oc::cdiv(kk, 4 * c.V);
+    c.cps = (int)oc::cdiv(kk, 4);
   }
   if (c.v2) {
     const oc::Sp3Cfg sc = oc::sp3_pick(t->M[l - 1], kk, nn);
@@ -1278,14 +1229,15 @@ void dispatch_tile(const oc_octree* t, int l, int K, const float* x, int kk, con
       sum_split(part, sc.splits, t->N[l] * (int64_t)nn, out, relu, s);
     return;
   }
-#define OC_TILE(K_, V_, MR_, NR_, WM_, VEC_)                                                    \
-  if (K == K_ && c.V == V_ && c.MR == MR_ && c.NR == NR_ && c.WM == WM_ && c.VEC == VEC_) {     \
-    launch_tile<K_, V_, MR_, NR_, WM_, FLIP, VEC_>(t, l, c, x, kk, w, nn, out, relu, part, s, ro, gate); \
-    return;                                                                                     \
+#define OC_TILE(K_, MR_, NR_, WM_, VEC_)                                                      \
+  if (K == K_ && c.MR == MR_ && c.NR == NR_ && c.WM == WM_ && c.VEC == VEC_) {                \
+    launch_tile<K_, MR_, NR_, WM_, FLIP, VEC_>(t, l, c, x, kk, w, nn, out, relu, part, s, ro, \
+                                               gate);                                         \
+    return;                                                                                   \
   }
-  OC_TILE(3, 1, 2, 1, 4, true) OC_TILE(3, 1, 2, 1, 4, false)
-  OC_TILE(5, 1, 1, 1, 4, true) OC_TILE(5, 1, 1, 1, 4, false)
-  OC_TILE(5, 1, 1, 2, 4, true) OC_TILE(5, 1, 1, 2, 4, false)
+  OC_TILE(3, 2, 1, 4, true) OC_TILE(3, 2, 1, 4, false)
+  OC_TILE(5, 1, 1, 4, true) OC_TILE(5, 1, 1, 4, false)
+  OC_TILE(5, 1, 2, 4, true) OC_TILE(5, 1, 2, 4, false)
 #undef OC_TILE
 }
 
@@ -1478,7 +1430,7 @@ void conv_s1_kernel_name(const oc_octree* t, int l, int K, int cin, int cout, in
     sp5_fwd_name(pass == 1, buf, n);
     return;
   }
-  snprintf(buf, n, "k_conv_tile<%d, %d, %d, %d, %d, %s, %s>", K, c.V, c.MR, c.NR, c.WM,
+  snprintf(buf, n, "k_conv_tile<%d, %d, %d, %d, %s, %s>", K, c.MR, c.NR, c.WM,
            pass == 0 ? "false" : "true", c.VEC ? "true" : "false");
 }
 

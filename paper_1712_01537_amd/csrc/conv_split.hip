@@ -21,18 +21,6 @@ bool rows_big(const oc_octree* t, int l, int c) {
   return t->N[l] * c * 4 >= int64_t(1) << 32;
 }
 
-// A 16x16 MFMA result held as D[4(l/16)+j][l%16] in lane l (j = 0..3) is
-// handed over so that lane l holds D[4(l%4)+j][l/4]: with rows l%16 of the
-// result as output rows, consecutive lanes then store consecutive 16 bytes.
-__device__ __forceinline__ v4f store_order(v4f d, int lane) {
-  const int src = (((lane & 3) << 4) + (lane >> 2)) << 2;  // byte lane index
-  v4f r;
-#pragma unroll
-  for (int j = 0; j < 4; ++j)
-    r[j] = __int_as_float(__builtin_amdgcn_ds_bpermute(src, __float_as_int(d[j])));
-  return r;
-}
-
 // Raw buffer resource over `bytes` bytes at p: loads past its end return zeros.
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const void* p, uint32_t bytes) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, bytes, 0x00020000);
@@ -379,7 +367,7 @@ __global__ __launch_bounds__(TB) __attribute__((amdgpu_waves_per_eu(2))) void k_
     }
     const int n = n0 + 4 * (lane & 3);
     const int64_t row = 8 * gt + 16 * rb + (lane >> 2);
-    v4f sv = store_order(v, lane);
+    v4f sv = oc::store_order(v, lane);
     if (n < nn && row < 8 * g1) {
       if (!split && relu) {
 #pragma unroll

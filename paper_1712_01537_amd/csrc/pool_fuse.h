@@ -1,4 +1,5 @@
-// 2x2x2 max-pooling in the epilogue of the stride-1 convolution kernels
+// Epilogues of the stride-1 convolution kernels: the order in which a result
+// is stored, and 2x2x2 max-pooling
 // (conv + ReLU + pooling in one pass: the depth-l output is never written).
 // Their 16x16 MFMA accumulators hold, in lane l, four output channels
 // 4(l/16) .. 4(l/16)+3 of octant row l%16 of a 16-row block; a block is two
@@ -47,6 +48,18 @@ __device__ __forceinline__ float pool_scan(const float* lds, int lane, uint32_t&
   }
   child = a;
   return m;
+}
+
+// A 16x16 MFMA result held as D[4(l/16)+j][l%16] in lane l (j = 0..3) is
+// handed over so that lane l holds D[4(l%4)+j][l/4]: with rows l%16 of the
+// result as output rows, consecutive lanes then store consecutive 16 bytes.
+__device__ __forceinline__ pf_v4f store_order(pf_v4f d, int lane) {
+  const int src = (((lane & 3) << 4) + (lane >> 2)) << 2;  // byte lane index
+  pf_v4f r;
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+    r[j] = __int_as_float(__builtin_amdgcn_ds_bpermute(src, __float_as_int(d[j])));
+  return r;
 }
 
 }  // namespace oc

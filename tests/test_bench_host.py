@@ -42,7 +42,7 @@ def test_peak_of_split_products():
         assert bench.mfma_peak(k, False) == pytest.approx(split, rel=1e-3)
     assert bench.mfma_peak("k_conv_bfw<5, 2, true, 8, 4, false>", True) == 2500.0
     assert bench.mfma_peak("k_cin_fwd<3, true>", False) == 157.3
-    assert bench.mfma_peak("k_conv_tile<5, 1, 1, 2, 4, true, true>", False) == 157.3
+    assert bench.mfma_peak("k_conv_tile<5, 1, 2, 4, true, true>", False) == 157.3
     # 1 ms at 157.3 and 1 ms at 2500 TFLOP/s
     assert bench.mean_peak([(157.3, 157.3), (2500.0, 2500.0)]) == pytest.approx((157.3 + 2500) / 2)
     r = bench.op_rate("conv_fwd", 2e9, 10.0, False, split)  # 200 TFLOP/s
