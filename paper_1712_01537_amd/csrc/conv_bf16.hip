@@ -661,9 +661,9 @@ struct BfwShape {
 // k_sp_wprep writes it, and the workgroup walks all chunks of the 6 kk virtual
 // channels, its sums staying in registers; *bad = 1 when an output is infinite
 // or NaN.
-// 5x5x5, 64 -> 64, 8 shapes at depth 6: 850 us, 162 TFLOP/s of fp32 products
-// (0.97 PFLOP/s of bf16 ones, the rate of the bf16 layer); the fp32 MFMA kernel
-// ran at about 67.  Splitting the input takes 19 us.
+// 64 -> 64 on 20305 groups of depth 6: 820 us, 203 TFLOP/s of fp32 products
+// (1.22 PFLOP/s of bf16 ones); the whole call, with the fp32 MFMA kernel, took
+// 1824.  Splitting the input takes 19 us.
 template <int K, int HC, bool FLIP, int GT_, int NW_, bool SP>
 __global__ __launch_bounds__(NW_ * 64, 8 / NW_) void k_conv_bfw(const int32_t* __restrict__ nbr, int64_t ngroups,
                                                    const uint16_t* __restrict__ x, int kk,
@@ -1386,8 +1386,9 @@ bool sp5_fwd_ok(const oc_octree* t, int l, int K, int kk, int nn) {
   // A tile of 8 groups and 64 columns is one workgroup's serial work over the
   // whole reduction (about 160 us at 64 channels, however few tiles there are),
   // while the fp32 kernel's time goes with the groups: 192 us at 1827 groups
-  // (229 tiles), 342 at 3249, where this one takes 166.  Columns that are no
-  // whole blocks of 64 would be multiplied as padding.
+  // (229 tiles), 342 at 3249, where this one takes 166.  The kernel has no masks
+  // for columns: layers without whole blocks of 64 stay on the fp32 kernel (64 ->
+  // 48 on 20305 groups: 1777 us, where 64 -> 64 takes 820 here).
   return K == 5 && kk % 32 == 0 && nn % 64 == 0 && sp5_fits(t, l, kk) &&
          cdiv(t->M[l - 1], BFW_GT) * (nn / 64) >= cu_count();
 }
@@ -1423,9 +1424,16 @@ void sp5_fwd_name(bool flip, char* buf, size_t n) {
 }
 
 bool sp5_dw_ok(const oc_octree* t, int l, int K, int cin, int cout) {
-  // 64 x 64 channel blocks without padding, and as many groups as the forward
-  // (3249 groups, 64 -> 64: 176 us, the fp32 kernel 400; 9205 groups, 128 -> 128:
-  // 1629 and 3735).  The error against 64 bits at 159111 groups is 1.1e-6 (4.9e-6).
+  // 64 x 64 channel blocks, for which the kernel has no masks, and as many groups
+  // as the forward, below which the two kernels were not compared (3249 groups, 64
+  // -> 64: 176 us, the fp32 kernel 400; 9205 groups, 128 -> 128: 1629 and 3735).
+  //
+  // A range's sums are running sums of MFMAs, which cut off downwards, so the
+  // error grows as the ranges get longer: with the groups, and with the channels,
+  // whose blocks leave fewer ranges.  It stays below the fp32 kernel's, against 64
+  // bits in the middle tap (fp32 in brackets): 159111 groups 64 -> 64 1.2e-6
+  // (4.9e-6), 128 -> 128 2.4e-6 (9.2e-6), 256 -> 256 5.2e-6 (1.4e-5; all values
+  // positive 6.5e-6, 3.1e-5); 66721 groups 512 -> 512, one range, 4.7e-6 (1.3e-5).
   return K == 5 && cin % 64 == 0 && cout % 64 == 0 && sp5_fits(t, l, std::max(cin, cout)) &&
          cdiv(t->M[l - 1], 8) >= cu_count();
 }

@@ -47,8 +47,6 @@ __device__ __forceinline__ v4u tr2(const char* p, int next) {
 // l supplies channels 8 (q & 1) .. + 7 of the pair's first (q < 2) or second
 // tap, q = l / 16.  The 27 taps make 14 pairs: x-offsets 0 and 1 at each of
 // the nine (y, z), then y-offsets 0 and 1 at x-offset 2, then the last three.
-// Each wave keeps the parts of its 16 output channels' weights in registers
-// for the whole launch (14 x 3 x 4 per lane), so the LDS holds x alone.
 //
 // A workgroup has eight waves: WN blocks of 16 output channels, WM = 4 / WN
 // shares of the row blocks, and two halves of the tap pairs, whose sums meet
@@ -86,15 +84,16 @@ __device__ __forceinline__ v4u tr2(const char* p, int next) {
 // address and so puts them in scratch memory (16 -> 64 pooled, 69765 groups: 492
 // us instead of 190).
 //
-// Measured on an MI355X (main kernel alone, 32 shapes at depth 6; before: the
-// fp32 MFMA kernel this one replaced, 16x16x4, weights in registers): 16->64
-// channels on 67121 groups 135 us, 220 TFLOP/s of fp32 products; 32->64 on 4434
-// groups 28 us (42); 16->16 on 218768 groups of depth 8 220 us (270).  At many
-// groups and 64 channels the MFMAs run at 1.4 PFLOP/s of bf16, about what a
-// large bf16 matrix product reaches here.  With few groups per workgroup (about
-// four tiles) the first loads and the weights' parts take 6 of 28 us; with 16
-// output channels the split and store of x (46 us of 61 at 67121 groups when
-// the MFMAs are left out), which four waves' columns would share, bound it.
+// Measured on an MI355X (this kernel alone, forward; before: the fp32 MFMA
+// kernel this one replaced, 16x16x4, weights in registers): 16->64 channels on
+// 67121 groups of depth 6 145 us, 205 TFLOP/s of fp32 products (pooled 151);
+// 32->64 on 4434 groups of depth 4 29 us (42); 16->16 on 211730 groups of depth
+// 8 174 us (270).  At many groups and 64 channels the MFMAs run at 1.25 PFLOP/s
+// of bf16; a plain bf16 matrix product reaches 1.24 at 8192 and 1.35 at 16384.
+// With few groups per workgroup (about four tiles) the first loads and the
+// weights' parts take 6 of 29 us; with 16 output channels the split and store
+// of x (46 us of 61 at 67121 groups when the MFMAs were left out), which four
+// waves' columns would share, bound it.
 constexpr int NST = 14;  // tap pairs
 struct Pair {
   int a, b;  // taps, b < 0: none
@@ -508,8 +507,9 @@ void launch_sp3(const oc_octree* t, int l, int splits, const float* x, int kk, c
 // the kernel before).
 //
 // Measured on an MI355X (before: an fp32 16x16x4 kernel of the same tiles):
-// 16 -> 16 channels on 218768 groups 174 us, 139 TFLOP/s of fp32 products; the
-// whole 24 -> 40 layer of 5 shapes at depth 6, three passes, 224 -> 189 us.
+// 16 -> 16 channels on 211730 groups of depth 8 208 us, 113 TFLOP/s of fp32
+// products, and 16 -> 64 on 67121 of depth 6 172 us, 173; the whole 24 -> 40
+// layer of 5 shapes at depth 6, three passes, 224 -> 182 us.
 // With 16 columns the split and store of x, which two halves' waves share with
 // 84 MFMAs each, bound it; with 32 the MFMAs do.
 template <int NBN, bool BIG>
@@ -631,8 +631,9 @@ __global__ __launch_bounds__(TB) __attribute__((amdgpu_waves_per_eu(2))) void k_
   // leave six times the fp32 kernel's error (3.8e-6 of dW at 218768 groups, 16 ->
   // 16).  The MFMA itself cuts its sums off, always downwards it seems: with dY
   // as it is in both halves, 1.5e-6 was left, growing with the octants as a bias
-  // does.  Half 1 therefore takes -dY, so that the two halves' biases cancel.  (Tap 27 of wave 3 reads tap
-  // 0's rows; its sum is dropped.)
+  // does.  Half 1 therefore takes -dY, so that the two halves' biases cancel:
+  // 2.1e-7, and 1.8e-6 for 256 -> 256 on 159111 groups (fp32 kernel 1.0e-5).  (Tap
+  // 27 of wave 3 reads tap 0's rows; its sum is dropped.)
   auto multiply = [&](int s) {
     constexpr int P = NBN == 1 ? 2 : 1, U = (NJ + P - 1) / P;
     const char* b = mine + (s & 1) * BUF;
