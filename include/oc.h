@@ -198,7 +198,13 @@ void oc_octree_free(oc_octree* tree);
  *              the neighbours of that position are read as usual) and
  *              written to that octant's row; rows of empty octants are
  *              zero.  Strided convolutions take ksize 3 only.
- *   dt      OC_F32: x, w fp32.  OC_BF16: x, w bf16 (round-to-nearest-even
+ *   dt      OC_F32: x, w fp32.  At stride 1 most layers form each product from
+ *           six bf16 matrix products (an operand is the exact sum of three bf16
+ *           values), with errors no larger than those of fp32 products over the whole
+ *           range of fp32 operands.  What that cannot represent (operands of
+ *           2^103 and more, sums of 2^80 and more, infinities, NaN) is formed
+ *           again with fp32 products, which takes longer.
+ *           OC_BF16: x, w bf16 (round-to-nearest-even
  *           values held as uint16); products accumulate in fp32, so the
  *           result is the fp32 convolution of the bf16 values.
  *   x       dev [N_l][cin].      w  dev [K^3][cin][cout].
@@ -206,6 +212,9 @@ void oc_octree_free(oc_octree* tree);
  *   ws      dev workspace of at least oc_conv_fwd_workspace() bytes (may be
  *           NULL when that is 0): partial sums of a reduction split across
  *           workgroups, added in a fixed order (results are reproducible);
+ *           for large OC_F32 layers with ksize 5 (cin a multiple of 32, cout of
+ *           64), copies of x and w in three bf16 parts (6 bytes per value of x,
+ *           1500 cin cout for w);
  *           for OC_BF16 shapes the bf16 matrix-core kernels do not take
  *           (strided; channel counts not multiples of 16; rows of x or of
  *           the output gradient spanning 2 GiB or more), x and w widened to
