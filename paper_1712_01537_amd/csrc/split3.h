@@ -7,8 +7,9 @@
 // 2^24 before they are split: a part is then a multiple of 2^-125, since an
 // fp32 value is one of 2^-149, and none is subnormal.  Sums of products are
 // multiplied by 2^-48 at the end; both factors are exact.  Without them a
-// value of 2^-120 keeps 14 of its bits.  A
-// product x w is then the sum of nine bf16 products, each exact in fp32.  Six
+// value of 2^-120 keeps 14 of its bits.
+//
+// A product x w is then the sum of nine bf16 products, each exact in fp32.  Six
 // are kept: lo hi', hi lo', mid mid', mid hi', hi mid', hi hi'.  Rounding to
 // nearest bounds mid by 2^-8 |x| and lo by 2^-17 |x|, so the three left out
 // are below 2^-24 |x w| together (2^-27 in the mean, of either sign), less
