@@ -140,7 +140,7 @@ def test_conv_split_parts(seed, B, n, depth, cin, cout):
 
 @pytest.mark.parametrize("cin,cout,where", [(16, 16, "x"), (20, 64, "x"), (32, 32, "w")])
 def test_conv_split_not_finite(cin, cout, where):
-    """Infinities, NaN and values whose bf16 rounding is infinite have no finite
+    """Infinities, NaN and values too large to be scaled and split have no finite
     parts; their results are those of plain fp32 products, and no other result
     changes."""
     oc = _oc()
@@ -674,8 +674,9 @@ def test_conv_small_bf16(K, stride):
     assert_dw_close(dw.cpu().numpy(), dwr, "dw bf16 inputs")
 
 
-DEFER_LAYERS = [  # K, stride, dtype, cin, cout: every weight-gradient path, and layers
-    # without a deferred form (strided; bf16 on the bf16 kernels)
+DEFER_LAYERS = [  # K, stride, dtype, cin, cout: every weight-gradient path that a small tree
+    # takes (K = 5 on three bf16 parts: test_conv_k5_deferred_dw), and layers without a
+    # deferred form (strided; bf16 on the bf16 kernels)
     (3, 1, torch.float32, 3, 16),     # first layer (Cin 3)
     (3, 1, torch.float32, 4, 32),     # first layer (Cin 4)
     (3, 1, torch.float32, 16, 32),    # matrix-core weight gradient, K = 3
