@@ -2,7 +2,8 @@
 device array (for callers that cannot allocate), through the C ABI: bit-for-
 bit the output of oc_conv_fwd on two calls in a row, the second smaller, so
 the second runs on the first's leftover scratch contents; calls whose
-workspace would exceed the array are refused."""
+workspace would exceed the array are refused, but for K = 5 fp32 layers, which
+then run on the fp32 kernel."""
 import ctypes as C
 
 import numpy as np
